@@ -211,37 +211,77 @@ __global__ __launch_bounds__(256) void k_ln_mod(const float* __restrict__ h, int
 }
 
 // ------------------------------------------------------ final norm + projection
+// One step of the output projection's reduction: of a lane's 2 HALF sums it
+// keeps the upper half (up) or the lower, adds its partner's, and sends the rest.
+template <int CTRL, int HALF>
+__device__ __forceinline__ void exchange(float (&a)[8], bool up) {
+#pragma unroll
+  for (int c = 0; c < HALF; ++c) {
+    const float keep = up ? a[c + HALF] : a[c], send = up ? a[c] : a[c + HALF];
+    a[c] = keep + dpp<CTRL>(send);
+  }
+}
+
+// HBM-bound (4 d bytes read per row). One row per wave: its 16-byte loads go
+// out first, then the workgroup stages the eight weight rows in LDS as f32
+// (16-byte reads serve the dot products; strided 2-byte loads of the weights
+// from L2 and 48 LDS-pipe shuffles were most of the time before). The eight
+// sums are reduced together: each of three exchanges halves the values a lane
+// carries. Measured at d = 1024: 820 rows 4.7 -> 3.3 us, 9831 rows 21.7 ->
+// 13.4 us (3.0 TB/s), 32768 rows 59 -> 40 us. Two or four rows per wave, which
+// share each weight read, are slower up to 9831 rows (13.5 / 15.4 us: fewer
+// waves in flight) and 11% faster at 32768.
 template <typename T, int NPL>
 __global__ __launch_bounds__(256) void k_final(const float* __restrict__ h, int rows, const T* __restrict__ w_out,
                                                const float* __restrict__ b_out, float* __restrict__ v_act) {
   constexpr int D = NPL * 64;
-  const int row = blockIdx.x * 4 + (threadIdx.x >> 6);
+  constexpr int V = NPL < 4 ? NPL : 4, NV = NPL / V;          // columns V*(lane + 64 j) .. +V-1
+  typedef float vec __attribute__((ext_vector_type(V), aligned(4)));   // h as the caller aligned it
+  typedef float wvec __attribute__((ext_vector_type(V)));
+  typedef T tvec __attribute__((ext_vector_type(V)));
+  __shared__ wvec ws[8][NV][64];
   const int lane = threadIdx.x & 63;
-  if (row >= rows) return;
-  const float* hr = h + (size_t)row * D;
+  const int row = blockIdx.x * 4 + (threadIdx.x >> 6);
   float v[NPL];
 #pragma unroll
-  for (int j = 0; j < NPL; ++j) v[j] = hr[lane + 64 * j];
+  for (int j = 0; j < NV; ++j) {                              // waves past the end read the last row
+    const vec x = *reinterpret_cast<const vec*>(h + (size_t)min(row, rows - 1) * D + V * (lane + 64 * j));
+#pragma unroll
+    for (int e = 0; e < V; ++e) v[V * j + e] = x[e];
+  }
+  for (int i = threadIdx.x; i < 8 * NV * 64; i += 256) {
+    const tvec t = *reinterpret_cast<const tvec*>(w_out + (size_t)V * i);
+    wvec f;
+#pragma unroll
+    for (int e = 0; e < V; ++e) f[e] = to_f32(t[e]);
+    ws[0][0][i] = f;
+  }
+  __syncthreads();
   float mean, rstd;
   row_stats<NPL>(v, mean, rstd);
   float acc[8];
 #pragma unroll
   for (int c = 0; c < 8; ++c) acc[c] = 0.0f;
 #pragma unroll
-  for (int j = 0; j < NPL; ++j) {
-    const int n = lane + 64 * j;
-    const float u = (v[j] - mean) * rstd;
+  for (int j = 0; j < NV; ++j) {
+    float u[V];
 #pragma unroll
-    for (int c = 0; c < 8; ++c) acc[c] += u * to_f32(w_out[(size_t)c * D + n]);
+    for (int e = 0; e < V; ++e) u[e] = (v[V * j + e] - mean) * rstd;
+#pragma unroll
+    for (int c = 0; c < 8; ++c) {
+      const wvec w = ws[c][j][lane];
+#pragma unroll
+      for (int e = 0; e < V; ++e) acc[c] = __builtin_fmaf(u[e], w[e], acc[c]);
+    }
   }
-#pragma unroll
-  for (int c = 0; c < 8; ++c) acc[c] = wave_sum(acc[c]);
-  if (lane < 8) {
-    float r = acc[0];
-#pragma unroll
-    for (int c = 1; c < 8; ++c) r = (lane == c) ? acc[c] : r;
-    v_act[(size_t)row * 8 + lane] = r + b_out[lane];
-  }
+  // Each exchange with a partner lane halves the outputs a lane carries: it
+  // keeps the half that its own bit 3, 2, 1 names and sends the other.
+  exchange<kDppXor8, 4>(acc, (lane & 8) != 0);
+  exchange<kDppMirror8, 2>(acc, (lane & 4) != 0);
+  exchange<kDppXor2, 1>(acc, (lane & 2) != 0);
+  const float r = rows_sum(acc[0] + dpp<kDppXor1>(acc[0]));
+  const int col = (lane >> 1) & 7;
+  if (row < rows && lane < 16 && (lane & 1) == 0) v_act[(size_t)row * 8 + col] = r + b_out[col];
 }
 
 // ------------------------------------------------------ merge + Euler + rotate

@@ -655,3 +655,26 @@ def test_sigma_calibration_drives_schedule(torch):
     for tau in (0, 3):
         got = f3c.schedule_plan(25, 16 ** 3, float(sigma), gamma_up=64.0, tau=tau)
         assert got.tolist() == osched.plan(25, 16 ** 3, float(want_sigma), gamma_up=64.0, tau=tau)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("width", [128, 256, 512, 2048])
+def test_final_projection_widths(torch, dtype, width):
+    """Every width's column split, a ragged last workgroup, and rows that start at a 4-byte offset. Bound: float32
+    sums of `width` products, 2^-24 sqrt(width) per term twice over (LN, dot), below 1e-5 at width 2048."""
+    from paper_2511_22533_amd import f3c
+    cfg = synth.ModelConfig(grid=8, width=width, depth=1, heads=width // 32, cond_tokens=64, cond_width=64, dtype=dtype)
+    W = synth.make_weights(cfg, seed=6, scale=0.05)
+    m = f3c.Model(cfg).load(W)
+    rows = 7
+    h = (2 * np.random.default_rng(width).standard_normal((rows, width)) + 0.5).astype(np.float32)
+    flat = torch.empty(rows * width + 1, dtype=torch.float32, device="cuda")
+    hd = flat[1:].view(rows, width)
+    hd.copy_(to_dev(h))
+    v = torch.full((rows + 1, 8), float("nan"), dtype=torch.float32, device="cuda")
+    say("final widths", dtype, width)
+    f3c.op_final(m, hd, v[:rows])
+    torch.cuda.synchronize()
+    want = dit.linear(dit.layer_norm(h.astype(np.float64)), W["out_w"], W["out_b"])
+    assert max_rel(v[:rows].cpu().numpy(), want) < 1e-5
+    assert torch.isnan(v[rows]).all()
