@@ -1,5 +1,5 @@
 // Spatiotemporal Stability Criterion scoring and lowest-score selection
-// (Sec. 4.2, Eqs. 2, 6, 7; Algorithm 1, SSC) in two kernels.
+// (Sec. 4.2, Eqs. 2, 6, 7; Algorithm 1, SSC).
 //
 // k_score_stats streams the two velocity caches over the whole chip (one
 // 256-thread workgroup per 1024 tokens of a sample): V_i = ||v_cache_i|| and
@@ -9,12 +9,18 @@
 // (the magnitudes are never -0; NaN is ignored), so the per-sample extremes do
 // not depend on how the tokens are split.
 //
-// k_select runs one 1024-thread workgroup per sample: it reduces the partial
-// extremes, forms the score C_i = w_a * norm(A_i) + w_v * norm(V_i) and an
-// order-preserving 32-bit key (NaN -> largest) per token into LDS, finds the
-// key of rank c-1 by an exact 4 x 8-bit radix select, and scans the keys in
-// token order: a token is cached if its key is smaller, or equal and among the
-// first r equal keys, which reproduces a stable ascending sort truncated at c.
+// The score C_i = w_a * norm(A_i) + w_v * norm(V_i) gives an order-preserving
+// 32-bit key (NaN -> largest). From 8193 tokens a second grid-wide kernel
+// (k_keys) forms the keys and a 4096-bin histogram of the scores; below, the
+// selecting workgroup does both itself.
+//
+// k_select runs one 1024-thread workgroup per sample with the keys in
+// registers, each wave owning one contiguous run of tokens. The score bin that
+// holds rank c-1 comes from the histogram; the few keys of that bin are ranked
+// against each other (many equal scores: an exact 4 x 8-bit radix select
+// instead), which gives the key of rank c-1. A token is cached if its key is
+// smaller, or equal and among the first r equal keys in token order, which
+// reproduces a stable ascending sort truncated at c.
 #include <mutex>
 #include <vector>
 
@@ -28,11 +34,22 @@ namespace f3c {
 namespace {
 
 constexpr int kThreads = 1024;       // select: one workgroup per sample
+constexpr int kWaves = kThreads / 64;
 constexpr int kStatThreads = 256;    // score statistics: tokens streamed over the chip
 constexpr int kStatPer = 4;
 constexpr int kChunk = kStatThreads * kStatPer;
 constexpr int kMaxChunks = kMaxTokens / kChunk;
-static_assert(kMaxChunks <= 64, "the select kernel reduces the partial extremes in one wave");
+static_assert(kMaxChunks <= 64, "the partial extremes are reduced in one wave");
+constexpr int kBins = 4096;          // score bins: [0, 1) in steps of 2^-12, NaN and 1 in the last
+constexpr int kCandidates = 512;     // keys of one bin that are ranked against each other
+// One workgroup issues an instruction for 32768 tokens in 0.2 us, so for many
+// tokens the keys (two correctly rounded divisions each) and their histogram
+// are worth a grid-wide kernel of their own. Measured on MI355X, batch 1, all
+// kernels, keys in k_select / in k_keys: 8193 tokens 16.2 / 16.1 us, 16384
+// 17.6 / 17.0, 32768 35.0 / 24.8. (Four radix passes over keys in LDS: 4096
+// tokens 17.4 us, now 9.9; 8192 25.3, now 11.9; 32768 70.9, now 24.8.)
+constexpr int kFusedTokens = 8192;
+static_assert(kBins <= kFusedTokens, "the histogram lives in the sample's pos rows");
 
 __device__ __forceinline__ float sumsq8(const float4& a, const float4& b) {
   float s = 0.0f;
@@ -69,40 +86,38 @@ __device__ __forceinline__ float norm_term(float a, float lo, float hi) {
   return div_rn(__fsub_rn(a, lo), __fsub_rn(hi, lo));
 }
 
-// In-place exclusive prefix sum of v[0..n) (n <= 512) by wave 0: lane l
-// sums entries 8l .. 8l+7, the lanes scan their totals, then each lane
-// writes its entries' exclusive prefixes. Callers place barriers around it.
-__device__ void segment_exclusive_scan(int* v, int n, int lane, int wave) {
-  if (wave != 0) return;
-  int loc[8];
-  int sum = 0;
+__device__ __forceinline__ float score_of(const float2& va, const float4& ext, float w_a, float w_v) {
+  return __fadd_rn(__fmul_rn(w_a, norm_term(va.y, ext.z, ext.w)), __fmul_rn(w_v, norm_term(va.x, ext.x, ext.y)));
+}
+
+// Bin of a score's key. Scores are >= 0 (or NaN), so the key is the score's
+// bits with the sign bit set; the product is exact and both steps are
+// monotonic, so a smaller key never has a larger bin. fminf drops NaN.
+__device__ __forceinline__ int bin_of(uint32_t key) {
+  return (int)fminf(__uint_as_float(key & 0x7FFFFFFFu) * (float)kBins, (float)(kBins - 1));
+}
+
+// The sample's extremes (loV, hiV, loA, hiA) from its partials, by one wave.
+__device__ __forceinline__ float4 reduce_extremes(const float4* partial, int chunks, int lane) {
+  float4 m = lane < chunks ? partial[lane] : make_float4(INFINITY, -INFINITY, INFINITY, -INFINITY);
 #pragma unroll
-  for (int e = 0; e < 8; ++e) {
-    const int k = 8 * lane + e;
-    loc[e] = k < n ? v[k] : 0;
-    sum += loc[e];
+  for (int o = 32; o > 0; o >>= 1) {
+    m.x = fminf(m.x, __shfl_xor(m.x, o));
+    m.y = fmaxf(m.y, __shfl_xor(m.y, o));
+    m.z = fminf(m.z, __shfl_xor(m.z, o));
+    m.w = fmaxf(m.w, __shfl_xor(m.w, o));
   }
-  int x = sum;
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const int y = __shfl_up(x, o);
-    if (lane >= o) x += y;
-  }
-  int run = x - sum;
-#pragma unroll
-  for (int e = 0; e < 8; ++e) {
-    const int k = 8 * lane + e;
-    if (k < n) v[k] = run;
-    run += loc[e];
-  }
+  return m;
 }
 
 // (V_i, A_i) of every token of the samples with c_b > 0, and each
 // workgroup's extremes (loV, hiV, loA, hiA) at partial[b * chunks + chunk].
+// hist (may be null): [B][N] ints whose first kBins per sample are zeroed for
+// k_keys.
 __global__ __launch_bounds__(kStatThreads) void k_score_stats(const float* __restrict__ v_cache,
                                                              const float* __restrict__ v_prev, int N, Segs n_cache,
                                                              float2* __restrict__ va, float4* __restrict__ partial,
-                                                             int chunks) {
+                                                             int chunks, int32_t* __restrict__ hist) {
   __shared__ float4 red[kStatThreads / 64];
   const int b = blockIdx.y, chunk = blockIdx.x;
   if (n_cache.off[b] == 0) return;
@@ -118,6 +133,10 @@ __global__ __launch_bounds__(kStatThreads) void k_score_stats(const float* __res
     c1[j] = pc[1];
     p0[j] = pp[0];
     p1[j] = pp[1];
+  }
+  if (hist && chunk * kChunk < kBins) {
+#pragma unroll
+    for (int j = 0; j < kStatPer; ++j) hist[base + chunk * kChunk + j * kStatThreads + tid] = 0;
   }
   float loV = INFINITY, hiV = -INFINITY, loA = INFINITY, hiA = -INFINITY;
 #pragma unroll
@@ -155,18 +174,63 @@ __global__ __launch_bounds__(kStatThreads) void k_score_stats(const float* __res
   }
 }
 
-// FROM_SCORES: the keys come from caller-given scores (given [B][N]) instead
-// of the magnitude pairs; everything after the keys is the same.
-template <bool FROM_SCORES>
+// Score (when asked for), key and histogram of every token of the samples with
+// c_b > 0, one workgroup per chunk as in k_score_stats. A chunk's keys replace
+// its magnitude pairs: chunk c's 1024 keys start where its pairs did.
+__global__ __launch_bounds__(kStatThreads) void k_keys(float2* __restrict__ va, const float4* __restrict__ partial,
+                                                       int chunks, int N, float w_a, float w_v, Segs n_cache,
+                                                       int32_t* __restrict__ hist, float* __restrict__ score) {
+  __shared__ int bins[kBins];
+  __shared__ float4 ext_s;
+  const int b = blockIdx.y, chunk = blockIdx.x;
+  if (n_cache.off[b] == 0) return;
+  const int tid = threadIdx.x;
+  const size_t base = (size_t)b * N;
+  float2 p[kStatPer];
+#pragma unroll
+  for (int j = 0; j < kStatPer; ++j) p[j] = va[base + min(chunk * kChunk + j * kStatThreads + tid, N - 1)];
+  for (int i = tid; i < kBins; i += kStatThreads) bins[i] = 0;
+  if (tid < 64) {
+    const float4 m = reduce_extremes(partial + (size_t)b * chunks, chunks, tid);
+    if (tid == 0) ext_s = m;
+  }
+  wait_vm<0>();                                     // every pair of the chunk read before keys replace them
+  __syncthreads();
+  const float4 ext = ext_s;
+  uint32_t* keys = reinterpret_cast<uint32_t*>(va + base + (size_t)chunk * kChunk);
+#pragma unroll
+  for (int j = 0; j < kStatPer; ++j) {
+    const int l = j * kStatThreads + tid, i = chunk * kChunk + l;
+    if (i < N) {
+      const float cs = score_of(p[j], ext, w_a, w_v);
+      const uint32_t k = order_key(cs);
+      keys[l] = k;
+      if (score) score[base + i] = cs;
+      atomicAdd(&bins[bin_of(k)], 1);
+    }
+  }
+  __syncthreads();
+  for (int i = tid; i < kBins; i += kStatThreads)
+    if (bins[i]) atomicAdd(&hist[base + i], bins[i]);
+}
+
+enum KeySource { KEYS_READY, KEYS_FROM_STATS, KEYS_FROM_SCORES };
+
+// The selection. Wave w owns tokens w * 64 R .. (w + 1) * 64 R - 1 (R rounds
+// of 64, at most KR), so ranks in token order need only per-wave counts.
+//   KEYS_READY: k_keys left the keys in the workspace and the histogram in pos.
+//   KEYS_FROM_STATS: keys and histogram are formed here from the pairs.
+//   KEYS_FROM_SCORES: any float32 scores given; always the radix select.
+template <int SRC, int KR>
 __global__ __launch_bounds__(kThreads) void k_select(const float2* __restrict__ va, const float4* __restrict__ partial,
                                                      int chunks, int N, float w_a, float w_v, Segs n_cache, Segs act,
                                                      int32_t* __restrict__ idx_active, int32_t* __restrict__ pos,
                                                      float* __restrict__ score, const float* __restrict__ given) {
-  __shared__ uint32_t keys[kMaxTokens];
-  __shared__ int hist[256];
-  __shared__ int cnt_eq[kMaxTokens / 64], cnt_act[kMaxTokens / 64];   // per (round, wave)
-  __shared__ int sel[2];
-  __shared__ float4 ext;
+  __shared__ int bins[SRC == KEYS_FROM_STATS ? kBins : 256];
+  __shared__ uint32_t cand[kCandidates];
+  __shared__ int wave_cnt[2][kWaves];
+  __shared__ int sel[2], n_cand;
+  __shared__ float4 ext_s;
 
   const int b = blockIdx.x;
   const int tid = threadIdx.x;
@@ -183,133 +247,201 @@ __global__ __launch_bounds__(kThreads) void k_select(const float2* __restrict__ 
     return;
   }
 
-  if constexpr (FROM_SCORES) {
-    for (int i = tid; i < N; i += kThreads) keys[i] = order_key(given[base + i]);
+  const int R = (N + kThreads - 1) / kThreads;
+  const int i0 = wave * 64 * R + lane;              // this lane's token of round j: i0 + 64 j
+  uint32_t key[KR];                                 // past the end: 0, never looked at
+  if (tid == 0) n_cand = 0;
+  if constexpr (SRC == KEYS_READY) {
+#pragma unroll
+    for (int j = 0; j < KR; ++j) {
+      const int i = min(i0 + 64 * j, N - 1), ch = i / kChunk;
+      key[j] = reinterpret_cast<const uint32_t*>(va + base + (size_t)ch * kChunk)[i - ch * kChunk];
+    }
+  } else if constexpr (SRC == KEYS_FROM_SCORES) {
+#pragma unroll
+    for (int j = 0; j < KR; ++j) key[j] = order_key(given[base + min(i0 + 64 * j, N - 1)]);
   } else {
-    // The sample's extremes from the partials (chunks <= 64: one wave).
+    float2 p[KR];
+#pragma unroll
+    for (int j = 0; j < KR; ++j) p[j] = va[base + min(i0 + 64 * j, N - 1)];
+    for (int i = tid; i < kBins; i += kThreads) bins[i] = 0;
     if (wave == 0) {
-      float4 m = lane < chunks ? partial[(size_t)b * chunks + lane]
-                               : make_float4(INFINITY, -INFINITY, INFINITY, -INFINITY);
+      const float4 m = reduce_extremes(partial + (size_t)b * chunks, chunks, lane);
+      if (lane == 0) ext_s = m;
+    }
+    __syncthreads();
+    const float4 ext = ext_s;
 #pragma unroll
-      for (int o = 32; o > 0; o >>= 1) {
-        m.x = fminf(m.x, __shfl_xor(m.x, o));
-        m.y = fmaxf(m.y, __shfl_xor(m.y, o));
-        m.z = fminf(m.z, __shfl_xor(m.z, o));
-        m.w = fmaxf(m.w, __shfl_xor(m.w, o));
+    for (int j = 0; j < KR; ++j) {
+      const int i = i0 + 64 * j;
+      const float cs = score_of(p[j], ext, w_a, w_v);
+      key[j] = order_key(cs);
+      if (j < R && i < N) {
+        if (score) score[base + i] = cs;
+        atomicAdd(&bins[bin_of(key[j])], 1);
       }
-      if (lane == 0) ext = m;
-    }
-    __syncthreads();
-    const float loV = ext.x, hiV = ext.y, loA = ext.z, hiA = ext.w;
-
-    // Scores and order keys.
-    for (int i = tid; i < N; i += kThreads) {
-      const float2 p = va[base + i];
-      const float cs = __fadd_rn(__fmul_rn(w_a, norm_term(p.y, loA, hiA)), __fmul_rn(w_v, norm_term(p.x, loV, hiV)));
-      keys[i] = order_key(cs);
-      if (score) score[base + i] = cs;
     }
   }
   __syncthreads();
+  // whether this lane holds a token in round j
+  auto holds = [&](int j) { return j < R && i0 + 64 * j < N; };
 
-  // Radix select of the key with 0-based rank c-1. The keys of one sample
-  // mostly share their leading byte (scores lie in [0, 1]), so a wave first
-  // merges the lanes that share the bin of its lowest pending lane, twice,
-  // with one LDS atomic per merged bin (same-address atomics of one
-  // instruction would serialise); the lanes left add their own key.
-  const uint64_t below = (1ull << lane) - 1ull;   // lanes before this one
-  uint32_t prefix = 0, mask = 0;
-  int r = c;
-  for (int shift = 24; shift >= 0; shift -= 8) {
-    for (int i = tid; i < 256; i += kThreads) hist[i] = 0;
-    __syncthreads();
-    for (int i0 = 0; i0 < N; i0 += kThreads) {     // whole waves iterate together (ballots below)
-      const int i = i0 + tid;
-      const uint32_t k = i < N ? keys[i] : 0u;
-      const bool in = i < N && (k & mask) == prefix;
-      const int bin = (int)((k >> shift) & 255u);
-      uint64_t todo = __ballot(in);
+  uint32_t kstar = 0;                               // key of rank c-1
+  int r = c;                                        // cached tokens among the keys equal to kstar
+  bool found = false;
+  if constexpr (SRC != KEYS_FROM_SCORES) {
+    // The bin of rank c-1: four consecutive bins per thread, a scan over the
+    // wave, the waves before it added up.
+    int h[4], tot = 0;
 #pragma unroll
-      for (int it = 0; it < 2; ++it) {
-        if (!todo) break;
-        const int leader = __ffsll((unsigned long long)todo) - 1;
-        const int lb = __shfl(bin, leader);
-        const uint64_t same = __ballot(in && bin == lb);
-        if (lane == leader) atomicAdd(&hist[lb], __popcll(same));
-        todo &= ~same;
-      }
-      if ((todo >> lane) & 1ull) atomicAdd(&hist[bin], 1);
+    for (int e = 0; e < 4; ++e) {
+      h[e] = SRC == KEYS_READY ? pos[base + 4 * tid + e] : bins[4 * tid + e];
+      tot += h[e];
     }
-    __syncthreads();
-    if (wave == 0) {
-      // lane owns bins 4*lane .. 4*lane+3
-      int h0 = hist[4 * lane], h1 = hist[4 * lane + 1], h2 = hist[4 * lane + 2], h3 = hist[4 * lane + 3];
-      int tot = h0 + h1 + h2 + h3, x = tot;
+    int x = tot;
 #pragma unroll
-      for (int o = 1; o < 64; o <<= 1) {
-        int y = __shfl_up(x, o);
-        if (lane >= o) x += y;
-      }
-      int before = x - tot;
-      if (before < r && r <= x) {
-        int d = 4 * lane, cum = before;
-        if (cum + h0 >= r) { d += 0; }
-        else if (cum + h0 + h1 >= r) { d += 1; cum += h0; }
-        else if (cum + h0 + h1 + h2 >= r) { d += 2; cum += h0 + h1; }
-        else { d += 3; cum += h0 + h1 + h2; }
-        sel[0] = d;
-        sel[1] = r - cum;
-      }
+    for (int o = 1; o < 64; o <<= 1) {
+      const int y = __shfl_up(x, o);
+      if (lane >= o) x += y;
+    }
+    if (lane == 63) wave_cnt[0][wave] = x;
+    __syncthreads();
+    int before = x - tot;
+    for (int w = 0; w < wave; ++w) before += wave_cnt[0][w];
+    if (before < c && c <= before + tot) {
+      int d = 0;
+#pragma unroll
+      for (int e = 0; e < 3; ++e)
+        if (d == e && before + h[e] < c) {
+          before += h[e];
+          d = e + 1;
+        }
+      sel[0] = 4 * tid + d;
+      sel[1] = c - before;
     }
     __syncthreads();
-    prefix |= (uint32_t)sel[0] << shift;
-    mask |= 255u << shift;
-    r = sel[1];
+    const int bin = sel[0], rank = sel[1];          // rank (1-based) inside the bin
+#pragma unroll
+    for (int j = 0; j < KR; ++j)
+      if (holds(j) && bin_of(key[j]) == bin) {
+        const int a = atomicAdd(&n_cand, 1);
+        if (a < kCandidates) cand[a] = key[j];
+      }
     __syncthreads();
+    const int m = n_cand;
+    found = m <= kCandidates;
+    if (found) {
+      if (tid < m) {
+        const uint32_t k = cand[tid];
+        int less = 0, same = 0;
+        for (int i = 0; i < m; ++i) {
+          less += cand[i] < k;
+          same += cand[i] == k;
+        }
+        if (less < rank && rank <= less + same) {   // equal keys write the same values
+          sel[0] = (int)k;
+          sel[1] = rank - less;
+        }
+      }
+      __syncthreads();
+      kstar = (uint32_t)sel[0];
+      r = sel[1];
+    }
   }
-  const uint32_t kstar = prefix;   // key of rank c-1; r = cached tokens among keys == kstar
+  if (!found) {
+    // Radix select of the key with 0-based rank c-1. The keys may share most
+    // of their bytes, so a wave first merges the lanes that share the bin of
+    // its lowest pending lane, twice, with one LDS atomic per merged bin
+    // (same-address atomics of one instruction would serialise); the lanes
+    // left add their own key.
+    uint32_t prefix = 0, mask = 0;
+    for (int shift = 24; shift >= 0; shift -= 8) {
+      __syncthreads();
+      for (int i = tid; i < 256; i += kThreads) bins[i] = 0;
+      __syncthreads();
+#pragma unroll
+      for (int j = 0; j < KR; ++j) {
+        const bool in = holds(j) && (key[j] & mask) == prefix;
+        const int bin = (int)((key[j] >> shift) & 255u);
+        uint64_t todo = __ballot(in);
+#pragma unroll
+        for (int it = 0; it < 2; ++it) {
+          if (!todo) break;
+          const int leader = __ffsll((unsigned long long)todo) - 1;
+          const int lb = __shfl(bin, leader);
+          const uint64_t same = __ballot(in && bin == lb);
+          if (lane == leader) atomicAdd(&bins[lb], __popcll(same));
+          todo &= ~same;
+        }
+        if ((todo >> lane) & 1ull) atomicAdd(&bins[bin], 1);
+      }
+      __syncthreads();
+      if (wave == 0) {
+        // lane owns bins 4*lane .. 4*lane+3
+        int h0 = bins[4 * lane], h1 = bins[4 * lane + 1], h2 = bins[4 * lane + 2], h3 = bins[4 * lane + 3];
+        int tot = h0 + h1 + h2 + h3, x = tot;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+          int y = __shfl_up(x, o);
+          if (lane >= o) x += y;
+        }
+        int before = x - tot;
+        if (before < r && r <= x) {
+          int d = 4 * lane, cum = before;
+          if (cum + h0 >= r) { d += 0; }
+          else if (cum + h0 + h1 >= r) { d += 1; cum += h0; }
+          else if (cum + h0 + h1 + h2 >= r) { d += 2; cum += h0 + h1; }
+          else { d += 3; cum += h0 + h1 + h2; }
+          sel[0] = d;
+          sel[1] = r - cum;
+        }
+      }
+      __syncthreads();
+      prefix |= (uint32_t)sel[0] << shift;
+      mask |= 255u << shift;
+      r = sel[1];
+    }
+    kstar = prefix;
+  }
 
-  // Token-order scan. Token i = 1024 j + 64 w + lane is handled by lane
-  // `lane` of wave w in round j, so (j, w, lane) runs in token order. A token
-  // is cached when its key is below kstar, or equal and among the first r
-  // equal keys. Per (round, wave) counts of equal keys, then of active
-  // tokens, go through an exclusive scan in LDS; a lane's rank inside its
-  // wave is the popcount of the ballot below it. Loads and stores of one
-  // wave touch 64 consecutive tokens.
-  const int rounds = (N + kThreads - 1) / kThreads;
-  const int nw = kThreads / 64;
-  for (int j = 0; j < rounds; ++j) {
-    const int i = j * kThreads + tid;
-    const uint64_t eq = __ballot(i < N && keys[i] == kstar);
-    if (lane == 0) cnt_eq[j * nw + wave] = __popcll(eq);
+  // Token-order ranks. Per wave the counts of smaller and of equal keys; the
+  // waves before this one then give the equal keys and active tokens ahead of
+  // its run, and within the run both follow from ballots round by round.
+  int n_less = 0, n_eq = 0;
+#pragma unroll
+  for (int j = 0; j < KR; ++j) {
+    n_less += __popcll(__ballot(holds(j) && key[j] < kstar));
+    n_eq += __popcll(__ballot(holds(j) && key[j] == kstar));
+  }
+  if (lane == 0) {
+    wave_cnt[0][wave] = n_less;
+    wave_cnt[1][wave] = n_eq;
   }
   __syncthreads();
-  segment_exclusive_scan(cnt_eq, rounds * nw, lane, wave);
-  __syncthreads();
-  for (int j = 0; j < rounds; ++j) {
-    const int i = j * kThreads + tid;
-    const uint32_t k = i < N ? keys[i] : 0xFFFFFFFFu;
-    const bool is_eq = i < N && k == kstar;
-    const uint64_t eq = __ballot(is_eq);
-    const bool cached = k < kstar || (is_eq && cnt_eq[j * nw + wave] + __popcll(eq & below) < r);
-    const uint64_t act_mask = __ballot(i < N && !cached);
-    if (lane == 0) cnt_act[j * nw + wave] = __popcll(act_mask);
+  int less0 = 0, eq0 = 0;
+  for (int w = 0; w < wave; ++w) {
+    less0 += wave_cnt[0][w];
+    eq0 += wave_cnt[1][w];
   }
-  __syncthreads();
-  segment_exclusive_scan(cnt_act, rounds * nw, lane, wave);
-  __syncthreads();
-  for (int j = 0; j < rounds; ++j) {
-    const int i = j * kThreads + tid;
-    const uint32_t k = i < N ? keys[i] : 0xFFFFFFFFu;
-    const bool is_eq = i < N && k == kstar;
-    const uint64_t eq = __ballot(is_eq);
-    const bool cached = k < kstar || (is_eq && cnt_eq[j * nw + wave] + __popcll(eq & below) < r);
-    const bool active = i < N && !cached;
-    const uint64_t act_mask = __ballot(active);
-    if (i < N) {
-      const int a = row0 + cnt_act[j * nw + wave] + __popcll(act_mask & below);
-      pos[base + i] = active ? a : -1;
-      if (active) idx_active[a] = i;
+  less0 = __builtin_amdgcn_readfirstlane(less0);
+  eq0 = __builtin_amdgcn_readfirstlane(eq0);
+  int next = row0 + min(wave * 64 * R, N) - less0 - min(eq0, r);   // row of this wave's first active token
+  const uint64_t below = (1ull << lane) - 1ull;
+#pragma unroll
+  for (int j = 0; j < KR; ++j) {
+    const bool in = holds(j);
+    bool cached = key[j] < kstar;
+    const uint64_t eq = __ballot(in && key[j] == kstar);
+    if (eq) {
+      if ((eq >> lane) & 1ull) cached = eq0 + __popcll(eq & below) < r;
+      eq0 += __popcll(eq);
+    }
+    const uint64_t am = __ballot(in && !cached);
+    const int a = next + __popcll(am & below);
+    next += __popcll(am);
+    if (in) {
+      pos[base + i0 + 64 * j] = cached ? -1 : a;
+      if (!cached) idx_active[a] = i0 + 64 * j;
     }
   }
 }
@@ -382,16 +514,31 @@ hipError_t launch_select(const float* v_cache, const float* v_prev, int B, int N
   float2* va = static_cast<float2*>(workspace);
   float4* partial = reinterpret_cast<float4*>(static_cast<char*>(workspace) +
                                               (((size_t)B * N * sizeof(float2) + 255) & ~(size_t)255));
-  launch(k_score_stats, dim3(chunks, B), dim3(kStatThreads), 0, s, v_cache, v_prev, N, n_cache, va, partial, chunks);
-  launch(k_select<false>, dim3(B), dim3(kThreads), 0, s, (const float2*)va, (const float4*)partial, chunks, N, w_a,
-         w_v, n_cache, act, idx_active, pos, score, (const float*)nullptr);
+  const bool fused = N <= kFusedTokens;
+  launch(k_score_stats, dim3(chunks, B), dim3(kStatThreads), 0, s, v_cache, v_prev, N, n_cache, va, partial, chunks,
+         fused ? (int32_t*)nullptr : pos);
+  if (!fused)
+    launch(k_keys, dim3(chunks, B), dim3(kStatThreads), 0, s, va, (const float4*)partial, chunks, N, w_a, w_v, n_cache,
+           pos, score);
+  auto select = [&](auto kernel) {
+    launch(kernel, dim3(B), dim3(kThreads), 0, s, (const float2*)va, (const float4*)partial, chunks, N, w_a, w_v,
+           n_cache, act, idx_active, pos, score, (const float*)nullptr);
+  };
+  if (N <= 4 * kThreads) select(k_select<KEYS_FROM_STATS, 4>);
+  else if (fused) select(k_select<KEYS_FROM_STATS, 8>);
+  else if (N <= 16 * kThreads) select(k_select<KEYS_READY, 16>);
+  else select(k_select<KEYS_READY, 32>);
   return hipGetLastError();
 }
 
 hipError_t launch_select_scores(const float* scores, int B, int N, const Segs& n_cache, const Segs& act,
                                 int32_t* idx_active, int32_t* pos, hipStream_t s) {
-  launch(k_select<true>, dim3(B), dim3(kThreads), 0, s, (const float2*)nullptr, (const float4*)nullptr, 0, N, 0.0f,
-         0.0f, n_cache, act, idx_active, pos, (float*)nullptr, scores);
+  auto select = [&](auto kernel) {
+    launch(kernel, dim3(B), dim3(kThreads), 0, s, (const float2*)nullptr, (const float4*)nullptr, 0, N, 0.0f, 0.0f,
+           n_cache, act, idx_active, pos, (float*)nullptr, scores);
+  };
+  if (N <= 8 * kThreads) select(k_select<KEYS_FROM_SCORES, 8>);
+  else select(k_select<KEYS_FROM_SCORES, 32>);
   return hipGetLastError();
 }
 

@@ -678,3 +678,25 @@ def test_final_projection_widths(torch, dtype, width):
     want = dit.linear(dit.layer_norm(h.astype(np.float64)), W["out_w"], W["out_b"])
     assert max_rel(v[:rows].cpu().numpy(), want) < 1e-5
     assert torch.isnan(v[rows]).all()
+
+
+@pytest.mark.parametrize("N", [1, 63, 65, 1025, 4095, 4097, 8192, 8193, 9261, 16384, 16385, 27000, 32767])
+def test_select_edges(torch, N):
+    """Selection on both sides of every size at which its kernels change, bit-exact: spread scores, scores crowded
+    into one histogram bin (all but a far one), mostly equal scores, and NaN / infinite velocities."""
+    rng = np.random.default_rng(N)
+    B = 4
+    vc = rng.standard_normal((B, N, 8)).astype(np.float32)
+    vp = (vc + 0.1 * rng.standard_normal((B, N, 8))).astype(np.float32)
+    vc[1] = 1.0 + 1e-5 * vc[1]
+    vp[1] = vc[1]
+    vc[1, N // 2] *= 50.0
+    vc[2] = vc[2, :1]
+    vp[2] = vc[2]
+    vp[2, N // 3] += 1.0
+    vc[3, N // 2] = np.nan
+    vp[3, N // 3, 2] = np.inf
+    for omega in (0.7, 0.0):
+        for quotas in ([N // 3] * B, [min(1, N)] * B, [N - 1, 0, N // 2, N], [N - 1] * B):
+            say("select edges", N, omega, quotas)
+            _check_select(torch, vc, vp, quotas, omega)
