@@ -11,24 +11,29 @@
 // B operand without any data movement; the K-slot order of P (keys
 // 8*(e/4) + 4*(l/32) + e%4) is matched when the V^T fragment is read.
 //
-// Scores on the matrix-core path (bf16, 64-wide heads) come out of the MFMAs
-// already shifted: each score tile's accumulation starts from -m (the
-// reference max), so a probability costs one exponential (and, unless the
-// queries were stored multiplied by log2(e)/sqrt(hd), one multiply) plus its
-// bf16 conversion.
-//
-// Pipelining. bf16 with 64-wide heads (the transformer's case): K and V tiles
+// Pipelining, bf16 with 64-wide heads (the transformer's case): K and V tiles
 // go from global memory straight into five LDS buffers (four with key groups)
-// with 16-byte DMA loads issued three tiles ahead (two with key groups), and
-// the score product of tile t+1 is issued before the softmax and PV product of
-// tile t, so the matrix cores have independent work while the vector unit runs
-// the softmax. Other types and head sizes
-// fetch the next tile into registers while the current one is consumed and
-// write it to the other of two LDS buffers. One barrier per tile either way.
-// Only the last, ragged tile is masked. The running max is updated lazily:
-// the accumulators are rescaled only when some query's max grows by more than
-// 2^8 (in base-2 units), which keeps every unnormalised probability below 2^8
-// and the result unchanged up to rounding.
+// with 16-byte DMA loads issued three tiles ahead (two with key groups). The
+// step is cut into half tiles of 32 keys: while the vector unit takes the
+// probabilities of one half, the matrix cores take the scores of the next and
+// the PV product of the one before, interleaved instruction by instruction.
+//
+// What bounds it: at 32768 tokens the chip's power. With random operands the
+// clock drops to 1.7-1.9 GHz under this kernel (2.4 GHz on zeros, with the same
+// cycles), so work taken out counts for more than stalls taken out. Per 64
+// keys and 256 queries of a CU: 1857 -> 1453 cycles against 1224 that the MFMAs
+// alone take, from (a) the interleaving, (b) row sums on one small MFMA per
+// eight probabilities instead of four v_dot2 (each of which holds the matrix
+// pipe 16 cycles), (c) no wait on a tile's own sums, (d) 64 queries per wave,
+// which halves the LDS fragment reads and, with 512 queries per workgroup, the
+// DMA. 32768 tokens, 16 heads: 3797 -> 3388 us; 9831 tokens 414 -> 361 us.
+//
+// Other types and head sizes fetch the next tile into registers while the
+// current one is consumed and write it to the other of two LDS buffers; the
+// running max is updated lazily: the accumulators are rescaled only when some
+// query's max grows by more than 2^8 (in base-2 units), which keeps every
+// unnormalised probability below 2^8 and the result unchanged up to rounding.
+// One barrier per tile either way. Only the last, ragged tile is masked.
 //
 // Few query tiles (late cached steps: a few hundred active tokens) cannot fill
 // 256 CUs, so the key range may be split: each split writes its unnormalised
@@ -45,6 +50,16 @@ namespace f3c {
 namespace {
 
 constexpr int kBKV = 64;             // keys per LDS tile
+
+// f(std::integral_constant<int, I>) for I = 0 .. N - 1, unrolled.
+template <typename F, int... I>
+__device__ __forceinline__ void static_for_seq(F f, std::integer_sequence<int, I...>) {
+  (f(std::integral_constant<int, I>{}), ...);
+}
+template <int N, typename F>
+__device__ __forceinline__ void static_for(F f) {
+  static_for_seq(f, std::make_integer_sequence<int, N>{});
+}
 
 // max(a, b, c) as one v_max3_f32. fmaxf on MFMA results costs three
 // instructions each (both inputs are first quieted with v_max x, x, since the
@@ -78,11 +93,13 @@ __device__ __forceinline__ float max16(const f32x16& v) {
 typedef short i16x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) i16x4 lds_i16x4;
 constexpr float kRescaleLog2 = 8.0f;
-// DMA path: a tile's probabilities are taken against the running reference
-// max; when a lane's 32 probabilities sum to more than this, the reference is
-// moved to the tile's max and the tile recomputed (so every probability that
-// enters the PV product is at most 2^16).
-constexpr float kTileSumLimit = 65536.0f;
+// DMA path: probabilities are taken against a reference max that moves only
+// when a query's row sum passes this. Probabilities (bf16, the exponent range
+// of f32) and sums then stay finite, and their relative rounding does not
+// depend on the reference.
+constexpr float kRowSumLimit = 0x1p80f;
+// Raw passes: the first tile's max (base 2) and the smallest row sum they take.
+constexpr float kRawRange = 40.0f, kRawSumMin = 0x1p-60f;
 
 struct AttnArgs {
   Segs qs, ks;
@@ -106,13 +123,14 @@ struct AttnArgs {
 // groups' (max, sum, output) are merged through LDS at the end. Two groups
 // double the waves per query tile where query tiles are too few to fill the
 // chip.
+// QB: blocks of 32 queries per wave.
 // QS: the queries were stored multiplied by log2(e)/sqrt(hd) (scores come out
 // in base-2 units).
-template <typename T, int HD, int NW, int SITE, bool SPLIT, int KS = 1, bool QS = false>
-__global__ __launch_bounds__(64 * NW) void k_attn(AttnArgs p) {
+template <typename T, int HD, int NW, int SITE, bool SPLIT, int KS = 1, bool QS = false, int QB = 1>
+__global__ __launch_bounds__(64 * NW, QB) void k_attn(AttnArgs p) {
   constexpr int NT = 64 * NW;
   constexpr int QW = NW / KS;                // query waves
-  constexpr int BQ = 32 * QW;
+  constexpr int BQ = 32 * QB * QW;
   constexpr int ES = sizeof(T);
   constexpr int E = Mfma<T>::E;
   // bf16 with 64-wide heads: K and V tiles go global -> LDS directly (16-byte
@@ -123,6 +141,7 @@ __global__ __launch_bounds__(64 * NW) void k_attn(AttnArgs p) {
   // transpose read. Other types and head sizes stage through registers, with
   // V transposed on its way into LDS.
   constexpr bool DMA = ES == 2 && HD == 64;
+  static_assert(QB == 1 || (DMA && KS == 1 && !SPLIT), "query blocks need the matrix-core path");
   static_assert(KS == 1 || (KS == 2 && DMA && NW % 2 == 0 && !SPLIT),
                 "key groups need the matrix-core path and the whole key range");
   constexpr int NBUF = DMA ? (KS == 1 ? 5 : 4) : 2;
@@ -158,16 +177,17 @@ __global__ __launch_bounds__(64 * NW) void k_attn(AttnArgs p) {
   const int qt = tq - p.tile_off[b];
   const int q_begin = p.qs.off[b], nq = p.qs.off[b + 1] - q_begin;
   const int k_begin = p.ks.off[b], nk = p.ks.off[b + 1] - k_begin;
-  const int qi = qt * BQ + qw * 32 + r32;              // query of this lane (within the sample)
-  const bool q_ok = qi < nq;
+  const int qi = qt * BQ + qw * 32 * QB + r32;         // this lane's query (within the sample) in the wave's first block
 
   // Q^T as the B operand: lane reads 16 bytes of its query row per 32-byte slice.
-  u32x4 qf[NKS];
-  {
-    const char* qrow = p.q + ((size_t)(q_begin + (q_ok ? qi : 0)) * p.ldq + head * HD) * ES;
+  u32x4 qf[QB][NKS];
+#pragma unroll
+  for (int j = 0; j < QB; ++j) {
+    const int i = qi + 32 * j;
+    const char* qrow = p.q + ((size_t)(q_begin + (i < nq ? i : 0)) * p.ldq + head * HD) * ES;
 #pragma unroll
     for (int s = 0; s < NKS; ++s)
-      qf[s] = q_ok ? *reinterpret_cast<const u32x4*>(qrow + s * 32 + g * 16) : u32x4{0, 0, 0, 0};
+      qf[j][s] = i < nq ? *reinterpret_cast<const u32x4*>(qrow + s * 32 + g * 16) : u32x4{0, 0, 0, 0};
   }
 
   // Tile staging: K row-major, V transposed (pairs of keys per 32/64-bit write).
@@ -230,36 +250,55 @@ __global__ __launch_bounds__(64 * NW) void k_attn(AttnArgs p) {
   //      take 32 bytes from each of 4 consecutive rows)
   constexpr int DBLK = kBKV / 8;                       // 8-row blocks per tile
   constexpr int DQ = (DBLK + NW - 1) / NW;             // blocks per wave
-  // DMA addresses: scalar bases (this sample's first key row of this head) and
-  // 32-bit lane offsets, the same for every tile but for the key index (the
-  // host checks that nk rows of either operand stay below 2 GiB); M0 from
-  // wave-uniform values. Four vector instructions per tile instead of ten.
-  const char* kbase = p.k + ((size_t)k_begin * p.ldk + head * HD) * ES;
-  const char* vbase = p.v + ((size_t)k_begin * p.ldv + head * HD) * ES;
+  // DMA addresses: a buffer descriptor per operand over this sample's rows of
+  // this head, and 32-bit lane offsets, the same for every tile but for the
+  // tile's first row (the host checks that nk rows of either operand stay
+  // below 2 GiB). Rows past the last lie outside the descriptor and read as
+  // zero, so no lane clamps its row: two vector instructions per tile and 1 KiB
+  // block pair, and two registers.
   const uint32_t ldk_b = (uint32_t)p.ldk * ES, ldv_b = (uint32_t)p.ldv * ES;
   const uint32_t lds_u = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)lds;
   const int wave_u = __builtin_amdgcn_readfirstlane(wave);
+  auto descriptor = [&](const char* base, uint32_t ld_b) {
+    const uint64_t a = (uint64_t)base;
+    const uint32_t bytes = nk > 0 ? (uint32_t)(nk - 1) * ld_b + HD * ES : 0u;
+    return u32x4{(uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)a),
+                 (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)(a >> 32) & 0xffffu),
+                 (uint32_t)__builtin_amdgcn_readfirstlane(bytes), 0x00020000u};
+  };
+  const u32x4 kdesc = descriptor(p.k + ((size_t)k_begin * p.ldk + head * HD) * ES, ldk_b);
+  const u32x4 vdesc = descriptor(p.v + ((size_t)k_begin * p.ldv + head * HD) * ES, ldv_b);
+  uint32_t kofs[DQ], vofs[DQ];
+#pragma unroll
+  for (int q = 0; q < DQ; ++q) {
+    const int row = min(wave_u + NW * q, DBLK - 1) * 8 + (lane >> 3), phys = lane & 7;
+    kofs[q] = row * ldk_b + (uint32_t)((phys ^ ((row >> 1) & 7)) << 4);
+    vofs[q] = row * ldv_b + (uint32_t)((phys ^ (((row >> 1) & 1) << 2)) << 4);
+    asm("" : "+v"(kofs[q]), "+v"(vofs[q]));            // kept, not recomputed per tile
+  }
   auto fetch_dma = [&](int kv0, int stage, int k) {
 #pragma unroll
     for (int q = 0; q < DQ; ++q) {
       const int blk_u = min(wave_u + NW * q, DBLK - 1);
-      const int row = blk_u * 8 + (lane >> 3), phys = lane & 7;
-      const uint32_t key = (uint32_t)min(kv0 + row, nk - 1);
-      const uint32_t kofs = key * ldk_b + (uint32_t)((phys ^ ((row >> 1) & 7)) << 4);
-      const uint32_t vofs = key * ldv_b + (uint32_t)((phys ^ (((row >> 1) & 1) << 2)) << 4);
+      const uint32_t ko = kofs[q] + (uint32_t)kv0 * ldk_b, vo = vofs[q] + (uint32_t)kv0 * ldv_b;
       const uint32_t kl = lds_u + (uint32_t)((stage * KS + k) * KBUF + blk_u * 1024);
       const uint32_t vl = lds_u + (uint32_t)(VREG + (stage * KS + k) * VBUF + blk_u * 1024);
-      asm volatile("global_load_lds_dwordx4 %0, %1" : : "v"(kofs), "s"(kbase), "{m0}"(kl) : "memory");
-      asm volatile("global_load_lds_dwordx4 %0, %1" : : "v"(vofs), "s"(vbase), "{m0}"(vl) : "memory");
+      asm volatile("buffer_load_dwordx4 %0, %1, 0 offen lds" : : "v"(ko), "s"(kdesc), "{m0}"(kl) : "memory");
+      asm volatile("buffer_load_dwordx4 %0, %1, 0 offen lds" : : "v"(vo), "s"(vdesc), "{m0}"(vl) : "memory");
     }
   };
 
-  f32x16 oacc[HT];
+  f32x16 oacc[QB][HT];
+  float m_run[QB], l_run[QB];          // running max (raw logits), unnormalised sum
 #pragma unroll
-  for (int t = 0; t < HT; ++t)
+  for (int j = 0; j < QB; ++j) {
 #pragma unroll
-    for (int e = 0; e < 16; ++e) oacc[t][e] = 0.0f;
-  float m_run = -INFINITY, l_run = 0.0f;       // running max (raw logits), unnormalised sum
+    for (int t = 0; t < HT; ++t)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) oacc[j][t][e] = 0.0f;
+    m_run[j] = -INFINITY;
+    l_run[j] = 0.0f;
+  }
   const float c = p.scale_log2;
   // Key tiles [t_begin, t_end) of this split (balanced; empty when the sample
   // has fewer tiles than splits).
@@ -274,352 +313,388 @@ __global__ __launch_bounds__(64 * NW) void k_attn(AttnArgs p) {
   const int vi = lane & 15;
   const int vrow = vi >> 2, vswz = ((vi >> 3) & 1) << 2, vcol = 4 * (vi & 3) + 16 * ((lane >> 4) & 1);
 
-  // S^T tiles of the tile in buffer buf: rows = keys 32*kt + ..., cols = this
-  // wave's 32 queries.
-  auto qk = [&](int buf, f32x16 (&sacc)[2]) {
-    const char* Ks = lds + buf * (KBUF + VBUF);
-#pragma unroll
-    for (int kt = 0; kt < 2; ++kt) {
-#pragma unroll
-      for (int s = 0; s < NKS; ++s) {
-        const u32x4 kf = DMA ? *reinterpret_cast<const u32x4*>(Ks + (kt * 32 + r32) * KRS + (((2 * s + g) ^ kswz) << 4))
-                             : *reinterpret_cast<const u32x4*>(Ks + (kt * 32 + r32) * KRS + s * 32 + g * 16);
-#pragma unroll
-        for (int u = 0; u < MMA_PER_READ; ++u) {
-          typename Mfma<T>::frag a, bq;
-          if constexpr (ES == 2) {
-            a = __builtin_bit_cast(bf16x8, kf);
-            bq = __builtin_bit_cast(bf16x8, qf[s]);
-          } else {
-            a = __builtin_bit_cast(f32x4, kf)[u];
-            bq = __builtin_bit_cast(f32x4, qf[s])[u];
-          }
-          // the first instruction of each tile starts from a zero accumulator
-          sacc[kt] = Mfma<T>::mma(a, bq, (s == 0 && u == 0) ? f32x16{} : sacc[kt]);
-        }
-      }
+  if constexpr (DMA) {
+    // Software pipeline over half steps of 32 keys. Half step (i, h) takes the
+    // probabilities of half h of tile i on the vector unit while the matrix
+    // cores take the scores of the next 32 keys and the PV product of the
+    // 32 keys before: three independent pieces of work, written as 8 * QB groups of
+    // one MFMA and its share of the vector work, and a scheduling barrier
+    // after each group keeps them so. (Left to the compiler, the score
+    // product's MFMAs stood alone and the vector work gathered behind them:
+    // both waves of a SIMD then want the same unit at the same time.)
+    // Fragments are read from LDS LA groups before their MFMAs.
+    auto fence = [] { __builtin_amdgcn_sched_barrier(0); };
+    // Row sums of the probabilities as rounded for the PV product: one 16x16x32
+    // MFMA per fragment with a selector as its A operand. The fragment's lane
+    // l holds query l % 32, which that instruction takes for column l % 16 of
+    // K-group l / 16; row m selects the K-groups with the parity of m / 4, so
+    // that every element of lane l's result is the sum of query l % 32 over
+    // both key halves. (A v_dot2 per pair holds the matrix pipe 16 cycles, as
+    // long as this MFMA does for eight values.)
+    u32x4 sel;
+    {
+      const uint32_t w = ((lane >> 4) & 1) == ((lane >> 2) & 1) ? 0x3f803f80u : 0u;   // two ones
+      sel = u32x4{w, w, w, w};
     }
-  };
-
-  // Online softmax of tile t's scores and O^T += V^T P^T with V from buffer buf.
-  auto softmax_pv = [&](int t, int buf, f32x16 (&sacc)[2]) {
-    const int kv0 = t * kBKV;
-    const char* Vt = lds + buf * (KBUF + VBUF) + KBUF;
-
-    // Key of element e: kv0 + 32*kt + 8*(e/4) + 4*g + e%4. Mask the ragged tail.
-    if (kv0 + kBKV > nk) {
-#pragma unroll
-      for (int kt = 0; kt < 2; ++kt)
+    auto row_sum = [&](const bf16x8& f, const f32x4& acc) {
+      return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, sel), f, acc, 0, 0, 0);
+    };
+    typedef __attribute__((address_space(3))) const u32x4 lds_u32x4;
+    auto mma_k = [&](const u32x4& kf, const u32x4& q, const f32x16& acc) {
+      return Mfma<T>::mma(__builtin_bit_cast(bf16x8, kf), __builtin_bit_cast(bf16x8, q), acc);
+    };
+    // Keys of element e of half kt: kv0 + 8*(e/4) + 4*g + e%4; mask those past nk.
+    auto mask = [&](int t, int kt, f32x16& s) {
+      const int kv0 = t * kBKV + kt * 32;
+      if (kv0 + 32 > nk) {
 #pragma unroll
         for (int e = 0; e < 16; ++e)
-          if (kv0 + kt * 32 + 8 * (e >> 2) + 4 * g + (e & 3) >= nk) sacc[kt][e] = -INFINITY;
-    }
-    // Max over this lane's 32 scores (two independent v_max3 chains).
-    const float m0 = max16(sacc[0]), m1 = max16(sacc[1]);
-    float mx = max3(m0, m1, m1);
-    // Lazy rescale: move the reference max only when some score exceeds it by
-    // more than 2^8 (base 2). m_run is the same in lanes l and l ^ 32 (it only
-    // changes here, from the query's full max), so each lane tests its own
-    // 32 keys and the wave-wide vote covers the query's other 32; the
-    // exchange for the full max is needed only in the (rare) branch.
-    if (__builtin_amdgcn_ballot_w64((mx - m_run) * c > kRescaleLog2) != 0) {
-      mx = fmaxf(mx, __shfl_xor(mx, 32));
-      const float m_new = fmaxf(m_run, mx);
-      const float alpha = __builtin_amdgcn_exp2f((m_run - m_new) * c);
-      m_run = m_new;
-      l_run *= alpha;
-#pragma unroll
-      for (int u = 0; u < HT; ++u)
-#pragma unroll
-        for (int e = 0; e < 16; ++e) oacc[u][e] *= alpha;
-    }
-    const float mc = m_run * c;
-#pragma unroll
-    for (int kt = 0; kt < 2; ++kt)
-#pragma unroll
-      for (int e = 0; e < 16; ++e) {
-        const float pe = __builtin_amdgcn_exp2f(fmaf(sacc[kt][e], c, -mc));
-        sacc[kt][e] = pe;
-        if constexpr (ES == 4) l_run += pe;
-      }
-
-    // O^T += V^T P^T over the 64 keys.
-#pragma unroll
-    for (int kt = 0; kt < 2; ++kt)
-#pragma unroll
-      for (int u = 0; u < 16 / E; ++u) {
-        typename Mfma<T>::frag pf;
-        if constexpr (ES == 2) {
-#pragma unroll
-          for (int e = 0; e < 8; ++e) pf[e] = (bf16)sacc[kt][8 * u + e];
-          // Row sum of the probabilities as rounded for the PV product (v_dot2 with 1s).
-          const bf16x2 ones = {(bf16)1.0f, (bf16)1.0f};
-          l_run = __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(pf, pf, 0, 1), ones, l_run, false);
-          l_run = __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(pf, pf, 2, 3), ones, l_run, false);
-          l_run = __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(pf, pf, 4, 5), ones, l_run, false);
-          l_run = __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(pf, pf, 6, 7), ones, l_run, false);
-        } else {
-          pf = sacc[kt][u];
-        }
-#pragma unroll
-        for (int h = 0; h < HT; ++h) {
-          typename Mfma<T>::frag vf;
-          if constexpr (DMA) {
-            // keys kb..kb+3 and kb+8..kb+11 at column h*32 + (lane%32) through two
-            // transpose reads of the row-major V tile (K-slot order of P).
-            const int kb = kt * 32 + 16 * u + 4 * g, col = h * 32 + vcol;
-            const char* a0 = Vt + (kb + vrow) * (HD * ES) + ((((col >> 3) ^ vswz)) << 4) + (col & 7) * ES;
-            const auto lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4*)a0);
-            const auto hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4*)(a0 + 8 * HD * ES));
-            vf = __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
-          } else if constexpr (ES == 2) {
-            const char* vrow = Vt + (h * 32 + r32) * VRS;
-            const int key0 = kt * 32 + 16 * u + 4 * g;
-            const u32x2 lo = *reinterpret_cast<const u32x2*>(vrow + key0 * ES);
-            const u32x2 hi = *reinterpret_cast<const u32x2*>(vrow + (key0 + 8) * ES);
-            vf = __builtin_bit_cast(bf16x8, u32x4{lo[0], lo[1], hi[0], hi[1]});
-          } else {
-            const char* vrow = Vt + (h * 32 + r32) * VRS;
-            const int key = kt * 32 + 8 * (u >> 2) + 4 * g + (u & 3);
-            vf = *reinterpret_cast<const float*>(vrow + key * ES);
-          }
-          oacc[h] = Mfma<T>::mma(vf, pf, oacc[h]);
-        }
-      }
-  };
-  auto compute = [&](int t, int buf) {
-    f32x16 sacc[2];
-    qk(buf, sacc);
-    softmax_pv(t, buf, sacc);
-  };
-
-  if constexpr (DMA) {
-    // Five buffers, tile t in buffer (t - t_begin) % 5, loads three tiles
-    // ahead. Iteration t waits for tile t + 1 (tile t + 2 stays in flight);
-    // its barrier makes every wave's DMA visible and retires the buffer of
-    // tile t - 2 (last read by the PV product of iteration t - 1), which
-    // receives tile t + 3 (clamped: past the end the last tile is re-read).
-    // The matrix cores then take the scores of tile t + 1 and the PV product
-    // of tile t - 1 while the vector unit computes the probabilities of tile
-    // t: the three are independent, so the steady-state iteration is one
-    // basic block the scheduler can interleave. The first and last tiles are
-    // peeled. Probabilities use a reference max that moves only in the rare
-    // fix-up branch (kTileSumLimit), so no per-tile max is computed.
-    const bf16x2 ones = {(bf16)1.0f, (bf16)1.0f};
-    f32x16 minit;                        // -(reference max) * c in every slot
-#pragma unroll
-    for (int e = 0; e < 16; ++e) minit[e] = 0.0f;
-    auto qk2 = [&](int buf, f32x16 (&s)[2]) {
-      const char* Ks = lds + (buf * KS + kgrp) * KBUF;
-      u32x4 kf[2][NKS];
-#pragma unroll
-      for (int kt = 0; kt < 2; ++kt)
-#pragma unroll
-        for (int q = 0; q < NKS; ++q)
-          kf[kt][q] = *reinterpret_cast<const u32x4*>(Ks + (kt * 32 + r32) * KRS + (((2 * q + g) ^ kswz) << 4));
-      // All eight reads go out before the first MFMA (left to itself the
-      // scheduler pairs each read with its MFMAs, one LDS latency per pair).
-      __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-      for (int q = 0; q < NKS; ++q)
-#pragma unroll
-        for (int kt = 0; kt < 2; ++kt)
-          s[kt] = Mfma<T>::mma(__builtin_bit_cast(bf16x8, kf[kt][q]), __builtin_bit_cast(bf16x8, qf[q]),
-                               q == 0 ? minit : s[kt]);
-    };
-    // O^T += V^T P^T for the tile in buffer buf; keys kb..kb+3 and kb+8..kb+11
-    // at column h*32 + (lane%32) through two transpose reads of the row-major
-    // V tile (the K-slot order of P). As for the scores, every fragment read
-    // is issued before the first MFMA (2-3% faster at 9831 and 32768 tokens
-    // than the scheduler's read-per-MFMA order; same instructions and results).
-    auto pv2 = [&](int buf, const bf16x8 (&pf)[2][2]) {
-      const char* Vt = lds + VREG + (buf * KS + kgrp) * VBUF;
-      bf16x8 vfs[2][2][HT];
-#pragma unroll
-      for (int kt = 0; kt < 2; ++kt)
-#pragma unroll
-        for (int u = 0; u < 2; ++u)
-#pragma unroll
-          for (int h = 0; h < HT; ++h) {
-            const int kb = kt * 32 + 16 * u + 4 * g, col = h * 32 + vcol;
-            const char* a0 = Vt + (kb + vrow) * (HD * ES) + (((col >> 3) ^ vswz) << 4) + (col & 7) * ES;
-            const auto lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4*)a0);
-            const auto hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4*)(a0 + 8 * HD * ES));
-            vfs[kt][u][h] = __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
-          }
-      __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-      for (int kt = 0; kt < 2; ++kt)
-#pragma unroll
-        for (int u = 0; u < 2; ++u)
-#pragma unroll
-          for (int h = 0; h < HT; ++h) oacc[h] = Mfma<T>::mma(vfs[kt][u][h], pf[kt][u], oacc[h]);
-    };
-    // Keys of element e: kv0 + 32*kt + 8*(e/4) + 4*g + e%4; mask those past nk.
-    auto mask2 = [&](int t, f32x16 (&s)[2]) {
-      const int kv0 = t * kBKV;
-      if (kv0 + kBKV > nk) {
-#pragma unroll
-        for (int kt = 0; kt < 2; ++kt)
-#pragma unroll
-          for (int e = 0; e < 16; ++e)
-            if (kv0 + kt * 32 + 8 * (e >> 2) + 4 * g + (e & 3) >= nk) s[kt][e] = -INFINITY;
+          if (kv0 + 8 * (e >> 2) + 4 * g + (e & 3) >= nk) s[e] = -INFINITY;
       }
     };
-    // Probabilities 2^((s - m_run) c) as the bf16 P fragments (the shift is
-    // already in the accumulators; c is 1 with pre-scaled queries); returns their
-    // sum as rounded for the PV product (v_dot2 with ones).
-    auto probs = [&](const f32x16 (&s)[2], bf16x8 (&pf)[2][2]) {
-      // with key groups a group's only tile can lie past the end (all keys
-      // masked, max -inf): its probabilities are then 0
-      float part[4];                     // four independent accumulation chains
-#pragma unroll
-      for (int kt = 0; kt < 2; ++kt)
-#pragma unroll
-        for (int u = 0; u < 2; ++u) {
-#pragma unroll
-          for (int e = 0; e < 8; ++e)
-            pf[kt][u][e] = (bf16)__builtin_amdgcn_exp2f(QS ? s[kt][8 * u + e] : s[kt][8 * u + e] * c);
-          const bf16x8& f = pf[kt][u];
-          // the chain's first dot in the three-operand form with a zero
-          // accumulator (no register to clear first); the nop covers a dot
-          // result read by the next dot as its accumulator
-          float a;
-          {
-            const bf16x2 f01 = __builtin_shufflevector(f, f, 0, 1);
-            asm("v_dot2_f32_bf16 %0, %1, %2, 0\n\ts_nop 1" : "=v"(a) : "v"(f01), "v"(ones));
-          }
-          a = __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(f, f, 2, 3), ones, a, false);
-          a = __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(f, f, 4, 5), ones, a, false);
-          part[2 * kt + u] = __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(f, f, 6, 7), ones, a, false);
-        }
-      return (part[0] + part[1]) + (part[2] + part[3]);
-    };
-    // The query's max over this tile (both key halves of the wave).
-    auto tile_max = [&](const f32x16 (&s)[2]) {
-      const float m0 = max16(s[0]), m1 = max16(s[1]);
-      const float mx = max3(m0, m1, m1);
-      return fmaxf(mx, __shfl_xor(mx, 32));
-    };
-    // Rare: some lane's probabilities outgrew the reference; move it to the
-    // tile's max, rescale what was accumulated (including the PV product of
-    // the previous tile, issued before) and redo the tile.
-    auto fixup = [&](f32x16 (&s)[2], f32x16* next, bf16x8 (&pf)[2][2], float& lt) {
-      if (__builtin_amdgcn_ballot_w64(lt > kTileSumLimit) != 0) {
-        const float tm = fmaxf(tile_max(s), 0.0f);   // tile max above the reference
-        const float alpha = __builtin_amdgcn_exp2f(QS ? -tm : -tm * c);
-        m_run += tm;
-        l_run *= alpha;
-#pragma unroll
-        for (int u = 0; u < HT; ++u)
-#pragma unroll
-          for (int e = 0; e < 16; ++e) oacc[u][e] *= alpha;
-#pragma unroll
-        for (int e = 0; e < 16; ++e) {
-          minit[e] = -m_run;
-          s[0][e] -= tm;
-          s[1][e] -= tm;
-          if (next) {
-            next[0][e] -= tm;
-            next[1][e] -= tm;
-          }
-        }
-        lt = probs(s, pf);
-      }
-    };
-    auto bnext = [](int b, int k) { b += k; return b >= NBUF ? b - NBUF : b; };
+    // The shift by the reference max. Safe passes (one query block per wave): a
+    // score accumulation starts from -(reference max) (minit), so a probability
+    // is one exponential (after a multiply unless the queries were stored
+    // scaled), and the reference moves where a sum outgrows it. Raw passes (two
+    // blocks, which leave no registers for that): a probability is 2^(s c)
+    // outright. That is the same result up to rounding as long as every sum
+    // stays in a range; a workgroup where one does not takes its queries again
+    // in safe passes, one block after the other. (Known after the first tile as
+    // a rule, by its max: two safe passes take what 32-query waves take. A sum
+    // that leaves the range later costs the raw pass too: 3000 x 1000 keys with
+    // scores up to 1000, 512 queries per workgroup, 65 us.)
+    auto prob = [&](float s) { return __builtin_amdgcn_exp2f(QS ? s : s * c); };
     // Steps i = 0, 1, ...: this wave's tile is t_begin + KS*i + kgrp; stage i
-    // % NBUF holds the KS tiles of step i. Loads run DIST steps ahead; a step's
-    // barrier retires the stage of step i - 2 (read by the PV product of step
-    // i - 1 at the latest), which receives step i + DIST.
+    // % NBUF holds the KS tiles of step i. Step i's barrier makes tile i + 1
+    // readable and retires the stage of step i - 2, whose V fragments were
+    // last read in half step (i - 1, 0); it receives step i + DIST (past the
+    // end the last tile is read again, so that the wait counts stay fixed).
     constexpr int DIST = NBUF - 2;
     constexpr int DS = KS * 2 * DQ;                     // DMA instructions per step and wave
+    constexpr int SK = KS * KBUF;
+    static_assert(KBUF == VBUF, "one stage stride for keys and values");
     const int n_steps = (t_end - t_begin + KS - 1) / KS;
     auto tile_of = [&](int i) { return t_begin + KS * i + kgrp; };
     auto fetch_step = [&](int i, int stage) {
 #pragma unroll
       for (int k = 0; k < KS; ++k) fetch_dma(min((t_begin + KS * i + k) * kBKV, last_kv), stage, k);
     };
-    // Step i with S(i) in cur and P(i-1) in pprev: S(i+1) -> next, P(i) -> pcur.
-    auto mid = [&](int i, int buf, f32x16 (&cur)[2], f32x16 (&next)[2], const bf16x8 (&pprev)[2][2],
-                   bf16x8 (&pcur)[2][2], auto first) {
-      wait_vm<(DIST - 2) * DS>();
-      __syncthreads();
-      fetch_step(i + DIST, bnext(buf, DIST));
-      qk2(bnext(buf, 1), next);
-      if constexpr (!decltype(first)::value) pv2(bnext(buf, NBUF - 1), pprev);
-      float lt = probs(cur, pcur);
-      fixup(cur, next, pcur, lt);
-      l_run += lt;
-    };
-    // Last step i (its tiles maybe ragged or past the end): PV(i-1), P(i), then PV(i).
-    auto last = [&](int i, int buf, f32x16 (&cur)[2], const bf16x8 (&pprev)[2][2], bf16x8 (&pcur)[2][2],
-                    auto first) {
-      if constexpr (!decltype(first)::value) pv2(bnext(buf, NBUF - 1), pprev);
-      mask2(tile_of(i), cur);
-      float lt = probs(cur, pcur);
-      fixup(cur, nullptr, pcur, lt);
-      l_run += lt;
-      pv2(buf, pcur);
-    };
-    if (t_begin < t_end) {               // uniform over the workgroup
-      // Q first: otherwise the compiler, which does not see the DMA, keeps its
-      // wait for the Q fragments inside the loop as a full vmcnt(0).
-      __builtin_amdgcn_sched_barrier(0);
-      wait_vm<0>();
+    // Every query of block j in `qf`, its output (unnormalised), reference max
+    // and row sum. False: a raw pass left its range (the same for the workgroup).
+    auto pass = [&](auto pbc, const u32x4 (&qf)[decltype(pbc)::value][NKS], f32x16 (&oacc)[decltype(pbc)::value][HT],
+                    float (&m_run)[decltype(pbc)::value], float (&l_run)[decltype(pbc)::value]) {
+      constexpr int PB = decltype(pbc)::value;
+      constexpr bool RAW = PB > 1;
+      constexpr int LA = 4 / PB;
+      // Lane addresses of the fragment reads in the current K and V stages (the
+      // V^T fragment of keys kb..kb+3 and kb+8..kb+11 at column 32 h + lane % 32
+      // comes from two transpose reads of the row-major tile, the K-slot order
+      // of P); they move from stage to stage.
+      uint32_t kad[NKS], vad[HT];
 #pragma unroll
-      for (int i = 0; i < DIST; ++i) fetch_step(i, i);
-      wait_vm<(DIST - 1) * DS>();
-      __syncthreads();
-      f32x16 sa[2], sb[2];
-      bf16x8 pa[2][2], pb[2][2];
-      qk2(0, sa);
-      if (n_steps == 1) mask2(tile_of(0), sa);
-      m_run = tile_max(sa);              // reference max: the first tile's
-      {
-        const float sub = m_run == -INFINITY ? 0.0f : m_run;   // a key group's tile may lie past the end
-#pragma unroll
-        for (int e = 0; e < 16; ++e) {
-          minit[e] = -sub;
-          sa[0][e] -= sub;
-          sa[1][e] -= sub;
-        }
+      for (int q = 0; q < NKS; ++q) {
+        kad[q] = lds_u + (uint32_t)(kgrp * KBUF + r32 * KRS + (((2 * q + g) ^ kswz) << 4));
+        asm("" : "+v"(kad[q]));
       }
-      const std::true_type yes{};
-      const std::false_type no{};
-      if (n_steps == 1) {
-        last(0, 0, sa, pb, pa, yes);
-      } else {
-        mid(0, 0, sa, sb, pb, pa, yes);                // S(1) in sb, P(0) in pa
-        int i = 1, buf = 1;
-        if constexpr (NBUF == 5) {
-          // ten steps per round with literal stages: their offsets fold into the reads
-          for (; i + 10 < n_steps; i += 10) {
-            mid(i, 1, sb, sa, pa, pb, no);
-            mid(i + 1, 2, sa, sb, pb, pa, no);
-            mid(i + 2, 3, sb, sa, pa, pb, no);
-            mid(i + 3, 4, sa, sb, pb, pa, no);
-            mid(i + 4, 0, sb, sa, pa, pb, no);
-            mid(i + 5, 1, sa, sb, pb, pa, no);
-            mid(i + 6, 2, sb, sa, pa, pb, no);
-            mid(i + 7, 3, sa, sb, pb, pa, no);
-            mid(i + 8, 4, sb, sa, pa, pb, no);
-            mid(i + 9, 0, sa, sb, pb, pa, no);
+#pragma unroll
+      for (int h = 0; h < HT; ++h) {
+        const int col = h * 32 + vcol;
+        vad[h] = lds_u + (uint32_t)(VREG + kgrp * VBUF + (4 * g + vrow) * (HD * ES) + (((col >> 3) ^ vswz) << 4) +
+                                    (col & 7) * ES);
+        asm("" : "+v"(vad[h]));
+      }
+      auto rd_k = [&](int kt, int q) {             // keys 32 kt.., head columns 16 q..
+        return *(lds_u32x4*)(uintptr_t)(kad[q] + (uint32_t)(kt * 32 * KRS));
+      };
+      auto rd_v = [&](int kt, int m) {             // keys 32 kt + 16 (m >> 1).., output columns 32 (m & 1)..
+        const uint32_t a = vad[m & 1] + (uint32_t)((kt * 32 + 16 * (m >> 1)) * (HD * ES));
+        const auto lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4*)(uintptr_t)a);
+        const auto hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4*)(uintptr_t)(a + 8 * HD * ES));
+        return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+      };
+      f32x16 minit[PB];
+      f32x4 ls[PB];                                // row sums (every element the same)
+      float l_prev[PB];                            // the same without the newest probabilities
+      auto probs = [&](const f32x16 (&s)[PB], bf16x8 (&pr)[PB][2]) {
+#pragma unroll
+        for (int j = 0; j < PB; ++j)
+#pragma unroll
+          for (int u = 0; u < 2; ++u) {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) pr[j][u][e] = (bf16)prob(s[j][8 * u + e]);
+            ls[j] = row_sum(pr[j][u], ls[j]);
+          }
+      };
+      // Before the newest probabilities pr (of scores s) enter the PV product.
+      // Rare: some query's row sum has outgrown its reference; move the reference
+      // to the largest of these scores or to the sum so far, rescale what was
+      // accumulated and the scores taken since (next), and take pr again.
+      auto fixup = [&](f32x16 (&s)[PB], f32x16 (&next)[PB], bf16x8 (&pr)[PB][2]) {
+        if constexpr (RAW) return;
+        // (a NaN sum too: an infinity or NaN among one query's probabilities
+        // reaches the row sum of the query 16 lanes away, as 0 * inf)
+        if (__builtin_amdgcn_ballot_w64(!(ls[0][0] <= kRowSumLimit)) != 0) {
+#pragma unroll
+          for (int j = 0; j < PB; ++j) {
+            const float mx = max16(s[j]);
+            float tm = l_prev[j] > 1.0f ? __builtin_amdgcn_logf(l_prev[j]) : 0.0f;   // log2
+            if constexpr (!QS) tm /= c;
+            tm = fmaxf(tm, fmaxf(mx, __shfl_xor(mx, 32)));
+            const float alpha = __builtin_amdgcn_exp2f(QS ? -tm : -tm * c);
+            m_run[j] += tm;
+#pragma unroll
+            for (int u = 0; u < HT; ++u)
+#pragma unroll
+              for (int e = 0; e < 16; ++e) oacc[j][u][e] *= alpha;
+#pragma unroll
+            for (int e = 0; e < 16; ++e) {
+              minit[j][e] -= tm;
+              s[j][e] -= tm;
+              next[j][e] -= tm;
+            }
+            // each query's sum from its own lanes alone
+            float lt = 0.0f;
+#pragma unroll
+            for (int u = 0; u < 2; ++u)
+#pragma unroll
+              for (int e = 0; e < 8; ++e) {
+                pr[j][u][e] = (bf16)prob(s[j][8 * u + e]);
+                lt += (float)pr[j][u][e];
+              }
+            lt = l_prev[j] * alpha + (lt + __shfl_xor(lt, 32));
+            ls[j] = f32x4{lt, lt, lt, lt};
+            // one opaque tuple: seen as a splat, it makes the loop carry copies
+            asm("" : "+v"(ls[j]));
           }
         }
-        for (; i + 2 < n_steps; i += 2, buf = bnext(buf, 2)) {
-          mid(i, buf, sb, sa, pa, pb, no);
-          mid(i + 1, bnext(buf, 1), sa, sb, pb, pa, no);
+#pragma unroll
+        for (int j = 0; j < PB; ++j) l_prev[j] = ls[j][0];
+      };
+      int k_stage = 0, v_stage = 0, d_stage = DIST;       // stages of kad, of vad and of the next fetch
+      auto step_of = [](int& stage) {
+        const uint32_t d = stage == NBUF - 1 ? (uint32_t)(-(NBUF - 1) * SK) : (uint32_t)SK;
+        stage = stage == NBUF - 1 ? 0 : stage + 1;
+        return d;
+      };
+      auto advance_k = [&] {
+        const uint32_t d = step_of(k_stage);
+#pragma unroll
+        for (int q = 0; q < NKS; ++q) kad[q] += d;
+      };
+      auto advance_v = [&] {
+        const uint32_t d = step_of(v_stage);
+#pragma unroll
+        for (int h = 0; h < HT; ++h) vad[h] += d;
+      };
+      auto sync = [&](int i) {
+        wait_vm<(DIST - 2) * DS>();
+        __builtin_amdgcn_s_barrier();
+        fence();
+        fetch_step(i + DIST, d_stage);
+        d_stage = d_stage == NBUF - 1 ? 0 : d_stage + 1;
+      };
+      const f32x16 zero = {};
+      u32x4 kf[NKS];
+      bf16x8 vf[4];
+      f32x16 s0[PB], s1[PB];                       // scores of a tile's first and second 32 keys
+      bf16x8 p0[PB][2], p1[PB][2];                 // and their probabilities
+      // Half step (i, KT): scores next = S(i, 1) or S(i + 1, 0), PV of pprev =
+      // P(i - 1, 1) or P(i, 0), probabilities cur -> pcur of half KT of tile i.
+      // Group n: score MFMA (even) or PV MFMA (odd), fragment n / PB >> 1 for
+      // query block n % PB.
+      auto half = [&](auto ktc, const f32x16 (&cur)[PB], f32x16 (&next)[PB], const bf16x8 (&pprev)[PB][2],
+                         bf16x8 (&pcur)[PB][2]) {
+        constexpr int KT = decltype(ktc)::value;
+        float ex[16 * PB];
+        static_for<8 * PB>([&](auto nc) {
+          constexpr int n = decltype(nc)::value, grp = n / PB, j = n % PB, m = grp >> 1;
+          if constexpr (j == 0) {
+            if constexpr (KT == 0 && grp == 8 - LA) {
+              advance_k();
+              advance_v();
+            }
+            constexpr int ahead = (grp + LA) % 8, m2 = ahead >> 1, kt = grp + LA < 8 ? KT ^ 1 : KT;
+            if constexpr (ahead % 2 == 0) kf[m2] = rd_k(kt, m2);
+            else vf[m2] = rd_v(kt, m2);
+          }
+          if constexpr (grp % 2 == 0) next[j] = mma_k(kf[m], qf[j][m], m == 0 ? (RAW ? zero : minit[j]) : next[j]);
+          else oacc[j][m & 1] = Mfma<T>::mma(vf[m], pprev[j][m >> 1], oacc[j][m & 1]);
+          // Exponentials, their conversion one group later, the sum of a
+          // fragment one group after its last conversion; the last sum lies
+          // groups before the next half step's check of it.
+          constexpr int N = 16 * PB;
+          constexpr int E0 = n == 0 ? 0 : std::min(N, 3 * n + 1), E1 = std::min(N, 3 * n + 4);
+          constexpr int C0 = n < 2 ? 0 : std::min(N, 3 * n - 2) & ~1, C1 = n == 0 ? 0 : std::min(N, 3 * n + 1) & ~1;
+          constexpr int R0 = n < 2 ? 0 : n < 3 ? 0 : (std::min(N, 3 * n - 5) & ~1) / 8, R1 = C0 / 8;
+          static_for<E1 - E0>([&](auto k) {
+            constexpr int e = E0 + decltype(k)::value;
+            ex[e] = prob(cur[e >> 4][e & 15]);
+          });
+          static_for<C1 - C0>([&](auto k) {
+            constexpr int e = C0 + decltype(k)::value;
+            pcur[e >> 4][(e >> 3) & 1][e & 7] = (bf16)ex[e];
+          });
+          static_for<R1 - R0>([&](auto k) {
+            constexpr int u = R0 + decltype(k)::value;
+            ls[u >> 1] = row_sum(pcur[u >> 1][u & 1], ls[u >> 1]);
+          });
+          fence();
+        });
+      };
+      const std::integral_constant<int, 0> h0{};
+      const std::integral_constant<int, 1> h1{};
+      if (t_begin < t_end) {               // uniform over the workgroup
+        // Q first: otherwise the compiler, which does not see the DMA, keeps its
+        // wait for the Q fragments inside the loop as a full vmcnt(0).
+        fence();
+        wait_vm<0>();
+#pragma unroll
+        for (int i = 0; i < DIST; ++i) fetch_step(i, i);
+        wait_vm<(DIST - 1) * DS>();
+        // the last stage is not fetched before step 1's barrier
+        volatile int* flag = reinterpret_cast<volatile int*>(lds + (NBUF - 1) * SK);
+        if (RAW && tid == 0) *flag = 0;
+        __syncthreads();
+        // Tile 0's scores; the reference max is that tile's.
+#pragma unroll
+        for (int q = 0; q < NKS; ++q) {
+          const u32x4 k0 = rd_k(0, q), k1 = rd_k(1, q);
+#pragma unroll
+          for (int j = 0; j < PB; ++j) {
+            s0[j] = mma_k(k0, qf[j][q], q == 0 ? zero : s0[j]);
+            s1[j] = mma_k(k1, qf[j][q], q == 0 ? zero : s1[j]);
+          }
         }
-        if (i + 1 < n_steps) {
-          mid(i, buf, sb, sa, pa, pb, no);
-          last(i + 1, bnext(buf, 1), sa, pb, pa, no);
-        } else {
-          last(i, buf, sb, pa, pb, no);
+#pragma unroll
+        for (int j = 0; j < PB; ++j) {
+          if (n_steps == 1) {
+            mask(tile_of(0), 0, s0[j]);
+            mask(tile_of(0), 1, s1[j]);
+          }
+          const float m0 = max16(s0[j]), m1 = max16(s1[j]);
+          const float mx = max3(m0, m1, m1);
+          m_run[j] = fmaxf(mx, __shfl_xor(mx, 32));
+          if constexpr (!RAW) {
+            const float sub = m_run[j] == -INFINITY ? 0.0f : m_run[j];   // a key group's tile may lie past the end
+#pragma unroll
+            for (int e = 0; e < 16; ++e) {
+              minit[j][e] = -sub;
+              s0[j][e] -= sub;
+              s1[j][e] -= sub;
+            }
+          }
+          ls[j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+          l_prev[j] = 0.0f;
+        }
+        if constexpr (RAW) {
+          float far = 0.0f;
+#pragma unroll
+          for (int j = 0; j < PB; ++j) far = fmaxf(far, fabsf(m_run[j] * c));
+          if (__builtin_amdgcn_ballot_w64(!(far < kRawRange)) != 0) *flag = 1;
+        }
+        if (n_steps > 1) {
+          // (0, 0): S(0, 1) is there and no PV is due
+          if constexpr (RAW) __builtin_amdgcn_s_waitcnt(0xc07f);   // lgkmcnt(0): the flag
+          sync(0);
+          if constexpr (RAW) {
+            if (__builtin_amdgcn_readfirstlane(*flag) != 0) {
+              wait_vm<0>();
+              __syncthreads();
+              return false;
+            }
+          }
+          probs(s0, p0);
+          advance_k();
+#pragma unroll
+          for (int m = 0; m < LA / 2; ++m) {
+            kf[m] = rd_k(0, m);
+            vf[m] = rd_v(0, m);
+          }
+          fence();
+          fixup(s0, s1, p0);
+          half(h1, s1, s0, p0, p1);
+          for (int i = 1; i < n_steps - 1; ++i) {
+            sync(i);
+            fixup(s1, s0, p1);
+            half(h0, s0, s1, p1, p0);
+            fixup(s0, s1, p0);
+            half(h1, s1, s0, p0, p1);
+          }
+          // PV of the last P(i, 1), and the last tile's second scores
+          fixup(s1, s0, p1);
+#pragma unroll
+          for (int m = 0; m < 4; ++m) {
+            if (m >= LA / 2) {
+              vf[m] = rd_v(1, m);
+              kf[m] = rd_k(1, m);
+            }
+#pragma unroll
+            for (int j = 0; j < PB; ++j) {
+              oacc[j][m & 1] = Mfma<T>::mma(vf[m], p1[j][m >> 1], oacc[j][m & 1]);
+              s1[j] = mma_k(kf[m], qf[j][m], m == 0 ? (RAW ? zero : minit[j]) : s1[j]);
+            }
+          }
+          advance_v();
+        }
+        // Last tile (maybe ragged or past the end).
+        const int t = tile_of(n_steps - 1);
+#pragma unroll
+        for (int j = 0; j < PB; ++j) {
+          mask(t, 0, s0[j]);
+          mask(t, 1, s1[j]);
+        }
+        probs(s0, p0);
+        fixup(s0, s1, p0);
+#pragma unroll
+        for (int m = 0; m < 4; ++m) {
+          const bf16x8 v = rd_v(0, m);
+#pragma unroll
+          for (int j = 0; j < PB; ++j) oacc[j][m & 1] = Mfma<T>::mma(v, p0[j][m >> 1], oacc[j][m & 1]);
+        }
+        probs(s1, p1);
+        fixup(s1, s0, p1);
+#pragma unroll
+        for (int m = 0; m < 4; ++m) {
+          const bf16x8 v = rd_v(1, m);
+#pragma unroll
+          for (int j = 0; j < PB; ++j) oacc[j][m & 1] = Mfma<T>::mma(v, p1[j][m >> 1], oacc[j][m & 1]);
+        }
+#pragma unroll
+        for (int j = 0; j < PB; ++j) l_run[j] = ls[j][0];
+        // no DMA may still target this workgroup's LDS when it retires
+        wait_vm<0>();
+        if constexpr (RAW) {
+          bool in_range = true;            // false for a NaN sum
+#pragma unroll
+          for (int j = 0; j < PB; ++j) in_range = in_range && l_run[j] > kRawSumMin && l_run[j] < kRowSumLimit;
+          __syncthreads();                 // every wave past its last tile read
+          if (tid == 0) *flag = 0;
+          __syncthreads();
+          if (__builtin_amdgcn_ballot_w64(!in_range) != 0) *flag = 1;
+          __syncthreads();
+          const bool bad = __builtin_amdgcn_readfirstlane(*flag) != 0;
+          __syncthreads();                 // read by every wave before a safe pass fetches
+          return !bad;
         }
       }
-      // no DMA may still target this workgroup's LDS when it retires
-      wait_vm<0>();
+      return true;
+    };
+    if constexpr (QB == 1) {
+      pass(std::integral_constant<int, 1>{}, qf, oacc, m_run, l_run);
+    } else if (!pass(std::integral_constant<int, QB>{}, qf, oacc, m_run, l_run)) {
+      static_for<QB>([&](auto jc) {
+        constexpr int j = decltype(jc)::value;
+        f32x16 o[1][HT] = {};
+        float m[1] = {-INFINITY}, l[1] = {0.0f};
+        u32x4 q[1][NKS];
+#pragma unroll
+        for (int s = 0; s < NKS; ++s) q[0][s] = qf[j][s];
+        pass(std::integral_constant<int, 1>{}, q, o, m, l);
+        __syncthreads();                 // every wave past its last tile read
+#pragma unroll
+        for (int h = 0; h < HT; ++h) oacc[j][h] = o[0][h];
+        l_run[j] = l[0];
+      });
     }
     if constexpr (KS > 1) {
       // Merge the key groups' (max, sum, output) through LDS, in group order:
@@ -630,24 +705,133 @@ __global__ __launch_bounds__(64 * NW) void k_attn(AttnArgs p) {
 #pragma unroll
         for (int u = 0; u < HT; ++u)
 #pragma unroll
-          for (int e = 0; e < 16; ++e) xs[(16 * u + e) * 64 + lane] = oacc[u][e];
-        xs[16 * HT * 64 + lane] = m_run;
-        xs[(16 * HT + 1) * 64 + lane] = l_run;
+          for (int e = 0; e < 16; ++e) xs[(16 * u + e) * 64 + lane] = oacc[0][u][e];
+        xs[16 * HT * 64 + lane] = m_run[0];
+        xs[(16 * HT + 1) * 64 + lane] = l_run[0];
       }
       __syncthreads();
       if (kgrp == 1) return;
       const float m1 = xs[16 * HT * 64 + lane], l1 = xs[(16 * HT + 1) * 64 + lane];
-      const float mm = fmaxf(m_run, m1);
-      const float a0 = __builtin_amdgcn_exp2f((m_run - mm) * c);
+      const float mm = fmaxf(m_run[0], m1);
+      const float a0 = __builtin_amdgcn_exp2f((m_run[0] - mm) * c);
       const float a1 = m1 == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f((m1 - mm) * c);
 #pragma unroll
       for (int u = 0; u < HT; ++u)
 #pragma unroll
-        for (int e = 0; e < 16; ++e) oacc[u][e] = oacc[u][e] * a0 + xs[(16 * u + e) * 64 + lane] * a1;
-      l_run = l_run * a0 + l1 * a1;
-      m_run = mm;
+        for (int e = 0; e < 16; ++e) oacc[0][u][e] = oacc[0][u][e] * a0 + xs[(16 * u + e) * 64 + lane] * a1;
+      l_run[0] = l_run[0] * a0 + l1 * a1;
+      m_run[0] = mm;
     }
   } else {
+    // S^T tiles of the tile in buffer buf: rows = keys 32*kt + ..., cols = this
+    // wave's 32 queries.
+    auto qk = [&](int buf, f32x16 (&sacc)[2]) {
+      const char* Ks = lds + buf * (KBUF + VBUF);
+  #pragma unroll
+      for (int kt = 0; kt < 2; ++kt) {
+  #pragma unroll
+        for (int s = 0; s < NKS; ++s) {
+          const u32x4 kf = *reinterpret_cast<const u32x4*>(Ks + (kt * 32 + r32) * KRS + s * 32 + g * 16);
+  #pragma unroll
+          for (int u = 0; u < MMA_PER_READ; ++u) {
+            typename Mfma<T>::frag a, bq;
+            if constexpr (ES == 2) {
+              a = __builtin_bit_cast(bf16x8, kf);
+              bq = __builtin_bit_cast(bf16x8, qf[0][s]);
+            } else {
+              a = __builtin_bit_cast(f32x4, kf)[u];
+              bq = __builtin_bit_cast(f32x4, qf[0][s])[u];
+            }
+            // the first instruction of each tile starts from a zero accumulator
+            sacc[kt] = Mfma<T>::mma(a, bq, (s == 0 && u == 0) ? f32x16{} : sacc[kt]);
+          }
+        }
+      }
+    };
+
+    // Online softmax of tile t's scores and O^T += V^T P^T with V from buffer buf.
+    auto softmax_pv = [&](int t, int buf, f32x16 (&sacc)[2]) {
+      const int kv0 = t * kBKV;
+      const char* Vt = lds + buf * (KBUF + VBUF) + KBUF;
+
+      // Key of element e: kv0 + 32*kt + 8*(e/4) + 4*g + e%4. Mask the ragged tail.
+      if (kv0 + kBKV > nk) {
+  #pragma unroll
+        for (int kt = 0; kt < 2; ++kt)
+  #pragma unroll
+          for (int e = 0; e < 16; ++e)
+            if (kv0 + kt * 32 + 8 * (e >> 2) + 4 * g + (e & 3) >= nk) sacc[kt][e] = -INFINITY;
+      }
+      // Max over this lane's 32 scores (two independent v_max3 chains).
+      const float m0 = max16(sacc[0]), m1 = max16(sacc[1]);
+      float mx = max3(m0, m1, m1);
+      // Lazy rescale: move the reference max only when some score exceeds it by
+      // more than 2^8 (base 2). m_run[0] is the same in lanes l and l ^ 32 (it only
+      // changes here, from the query's full max), so each lane tests its own
+      // 32 keys and the wave-wide vote covers the query's other 32; the
+      // exchange for the full max is needed only in the (rare) branch.
+      if (__builtin_amdgcn_ballot_w64((mx - m_run[0]) * c > kRescaleLog2) != 0) {
+        mx = fmaxf(mx, __shfl_xor(mx, 32));
+        const float m_new = fmaxf(m_run[0], mx);
+        const float alpha = __builtin_amdgcn_exp2f((m_run[0] - m_new) * c);
+        m_run[0] = m_new;
+        l_run[0] *= alpha;
+  #pragma unroll
+        for (int u = 0; u < HT; ++u)
+  #pragma unroll
+          for (int e = 0; e < 16; ++e) oacc[0][u][e] *= alpha;
+      }
+      const float mc = m_run[0] * c;
+  #pragma unroll
+      for (int kt = 0; kt < 2; ++kt)
+  #pragma unroll
+        for (int e = 0; e < 16; ++e) {
+          const float pe = __builtin_amdgcn_exp2f(fmaf(sacc[kt][e], c, -mc));
+          sacc[kt][e] = pe;
+          if constexpr (ES == 4) l_run[0] += pe;
+        }
+
+      // O^T += V^T P^T over the 64 keys.
+  #pragma unroll
+      for (int kt = 0; kt < 2; ++kt)
+  #pragma unroll
+        for (int u = 0; u < 16 / E; ++u) {
+          typename Mfma<T>::frag pf;
+          if constexpr (ES == 2) {
+  #pragma unroll
+            for (int e = 0; e < 8; ++e) pf[e] = (bf16)sacc[kt][8 * u + e];
+            // Row sum of the probabilities as rounded for the PV product (v_dot2 with 1s).
+            const bf16x2 ones = {(bf16)1.0f, (bf16)1.0f};
+            l_run[0] = __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(pf, pf, 0, 1), ones, l_run[0], false);
+            l_run[0] = __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(pf, pf, 2, 3), ones, l_run[0], false);
+            l_run[0] = __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(pf, pf, 4, 5), ones, l_run[0], false);
+            l_run[0] = __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(pf, pf, 6, 7), ones, l_run[0], false);
+          } else {
+            pf = sacc[kt][u];
+          }
+  #pragma unroll
+          for (int h = 0; h < HT; ++h) {
+            typename Mfma<T>::frag vf;
+            if constexpr (ES == 2) {
+              const char* vrow = Vt + (h * 32 + r32) * VRS;
+              const int key0 = kt * 32 + 16 * u + 4 * g;
+              const u32x2 lo = *reinterpret_cast<const u32x2*>(vrow + key0 * ES);
+              const u32x2 hi = *reinterpret_cast<const u32x2*>(vrow + (key0 + 8) * ES);
+              vf = __builtin_bit_cast(bf16x8, u32x4{lo[0], lo[1], hi[0], hi[1]});
+            } else {
+              const char* vrow = Vt + (h * 32 + r32) * VRS;
+              const int key = kt * 32 + 8 * (u >> 2) + 4 * g + (u & 3);
+              vf = *reinterpret_cast<const float*>(vrow + key * ES);
+            }
+            oacc[0][h] = Mfma<T>::mma(vf, pf, oacc[0][h]);
+          }
+        }
+    };
+    auto compute = [&](int t, int buf) {
+      f32x16 sacc[2];
+      qk(buf, sacc);
+      softmax_pv(t, buf, sacc);
+    };
     // Fetches are unconditional (past the end they re-read the last tile), so
     // the wait before staging tile t+1 does not cover the loads of tile t+2.
     auto tile = [&](int t, int r) {      // r = (t - t_begin) & 1 (a constant at each call site)
@@ -670,39 +854,44 @@ __global__ __launch_bounds__(64 * NW) void k_attn(AttnArgs p) {
     }
   }
 
-  const float l_tot = l_run + __shfl_xor(l_run, 32);
-  if (!q_ok) return;
-  if constexpr (SPLIT) {
-    const size_t prow = ((size_t)sp * p.rows + (q_begin - p.qs.off[0] + qi)) * p.heads + head;
-    float* po = p.part_o + prow * HD;
 #pragma unroll
-    for (int h = 0; h < HT; ++h)
+  for (int j = 0; j < QB; ++j) {
+    const int i = qi + 32 * j;
+    // the matrix-core path's sums already cover both key halves of the wave
+    const float l_tot = DMA ? l_run[j] : l_run[j] + __shfl_xor(l_run[j], 32);
+    if (i >= nq) return;
+    if constexpr (SPLIT) {
+      const size_t prow = ((size_t)sp * p.rows + (q_begin - p.qs.off[0] + i)) * p.heads + head;
+      float* po = p.part_o + prow * HD;
 #pragma unroll
-      for (int q4 = 0; q4 < 4; ++q4)
-        *reinterpret_cast<float4*>(po + h * 32 + 8 * q4 + 4 * g) =
-            make_float4(oacc[h][4 * q4], oacc[h][4 * q4 + 1], oacc[h][4 * q4 + 2], oacc[h][4 * q4 + 3]);
-    if (g == 0) *reinterpret_cast<float2*>(p.part_ml + prow * 2) = make_float2(m_run * c, l_tot);
-    return;
-  }
-  const float inv = 1.0f / l_tot;
-  T* orow = reinterpret_cast<T*>(p.o + ((size_t)(q_begin + qi) * p.ldo + head * HD) * ES);
+      for (int h = 0; h < HT; ++h)
 #pragma unroll
-  for (int h = 0; h < HT; ++h)
+        for (int q4 = 0; q4 < 4; ++q4)
+          *reinterpret_cast<float4*>(po + h * 32 + 8 * q4 + 4 * g) = make_float4(
+              oacc[j][h][4 * q4], oacc[j][h][4 * q4 + 1], oacc[j][h][4 * q4 + 2], oacc[j][h][4 * q4 + 3]);
+      if (g == 0) *reinterpret_cast<float2*>(p.part_ml + prow * 2) = make_float2(m_run[j] * c, l_tot);
+    } else {
+      const float inv = 1.0f / l_tot;
+      T* orow = reinterpret_cast<T*>(p.o + ((size_t)(q_begin + i) * p.ldo + head * HD) * ES);
 #pragma unroll
-    for (int q4 = 0; q4 < 4; ++q4) {
-      float v[4];
+      for (int h = 0; h < HT; ++h)
 #pragma unroll
-      for (int e = 0; e < 4; ++e) v[e] = oacc[h][4 * q4 + e] * inv;
-      T* dst = orow + h * 32 + 8 * q4 + 4 * g;
-      if constexpr (ES == 2) {
-        bf16x4 o4;
+        for (int q4 = 0; q4 < 4; ++q4) {
+          float v[4];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) o4[e] = (bf16)v[e];
-        *reinterpret_cast<bf16x4*>(dst) = o4;
-      } else {
-        *reinterpret_cast<float4*>(dst) = make_float4(v[0], v[1], v[2], v[3]);
-      }
+          for (int e = 0; e < 4; ++e) v[e] = oacc[j][h][4 * q4 + e] * inv;
+          T* dst = orow + h * 32 + 8 * q4 + 4 * g;
+          if constexpr (ES == 2) {
+            bf16x4 o4;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) o4[e] = (bf16)v[e];
+            *reinterpret_cast<bf16x4*>(dst) = o4;
+          } else {
+            *reinterpret_cast<float4*>(dst) = make_float4(v[0], v[1], v[2], v[3]);
+          }
+        }
     }
+  }
 }
 
 // Merge of the key-range splits: one thread per (query row, head, 4 output
@@ -745,31 +934,32 @@ __global__ __launch_bounds__(256) void k_attn_combine(AttnArgs p) {
   }
 }
 
-template <typename T, int HD, int NW, int SITE, int KS = 1, bool QS = false>
+template <typename T, int HD, int NW, int SITE, int KS = 1, bool QS = false, int QB = 1>
 hipError_t launch_k(const AttnArgs& a, int tiles, hipStream_t s) {
   const dim3 block(64 * NW);
-  if constexpr (KS > 1) {
+  if constexpr (KS > 1 || QB > 1) {
     if (a.splits != 1) return hipErrorInvalidValue;
-    launch((k_attn<T, HD, NW, SITE, false, KS, QS>), dim3(tiles * a.heads), block, 0, s, a);
+    launch((k_attn<T, HD, NW, SITE, false, KS, QS, QB>), dim3(tiles * a.heads), block, 0, s, a);
+    return hipGetLastError();
+  } else {
+    if (a.splits == 1) {
+      launch((k_attn<T, HD, NW, SITE, false, 1, QS>), dim3(tiles * a.heads), block, 0, s, a);
+      return hipGetLastError();
+    }
+    launch((k_attn<T, HD, NW, SITE, true, 1, QS>), dim3(tiles * a.heads * a.splits), block, 0, s, a);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    const int64_t n = (int64_t)a.rows * a.heads * (HD / 4);
+    launch((k_attn_combine<T, HD>), dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, a);
     return hipGetLastError();
   }
-  if (a.splits == 1) {
-    launch((k_attn<T, HD, NW, SITE, false, 1, QS>), dim3(tiles * a.heads), block, 0, s, a);
-    return hipGetLastError();
-  }
-  launch((k_attn<T, HD, NW, SITE, true, 1, QS>), dim3(tiles * a.heads * a.splits), block, 0, s, a);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  const int64_t n = (int64_t)a.rows * a.heads * (HD / 4);
-  launch((k_attn_combine<T, HD>), dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, a);
-  return hipGetLastError();
 }
 
 // splits > 1 requires a.part_o / a.part_ml sized for them.
-template <int NW, int SITE, int KS = 1>
+template <int NW, int SITE, int KS = 1, int QB = 1>
 hipError_t launch_a(int dt, int hd, const AttnArgs& a0, int heads, int splits, hipStream_t s, bool qs) {
   AttnArgs a = a0;
-  constexpr int BQ = 32 * NW / KS;
+  constexpr int BQ = 32 * QB * NW / KS;
   a.tile_off[0] = 0;
   for (int b = 0; b < a.qs.B; ++b) a.tile_off[b + 1] = a.tile_off[b] + (a.qs.off[b + 1] - a.qs.off[b] + BQ - 1) / BQ;
   const int tiles = a.tile_off[a.qs.B];
@@ -777,18 +967,18 @@ hipError_t launch_a(int dt, int hd, const AttnArgs& a0, int heads, int splits, h
   a.heads = heads;
   a.splits = splits;
   a.rows = a.qs.off[a.qs.B] - a.qs.off[0];
-  if constexpr (KS > 1) {
-    if (dt == DT_BF16 && hd == 64)
-      return qs ? launch_k<bf16, 64, NW, SITE, KS, true>(a, tiles, s) : launch_k<bf16, 64, NW, SITE, KS>(a, tiles, s);
+  if (dt == DT_BF16 && hd == 64) {
+    if (qs) return launch_k<bf16, 64, NW, SITE, KS, true, QB>(a, tiles, s);
+    // the model's own calls always store their queries scaled
+    if constexpr (SITE == SITE_OP) return launch_k<bf16, 64, NW, SITE, KS, false, QB>(a, tiles, s);
     return hipErrorInvalidValue;
-  } else {
-    if (dt == DT_BF16 && hd == 64)
-      return qs ? launch_k<bf16, 64, NW, SITE, 1, true>(a, tiles, s) : launch_k<bf16, 64, NW, SITE>(a, tiles, s);
+  }
+  if constexpr (KS == 1 && QB == 1) {
     if (dt == DT_BF16 && hd == 32) return launch_k<bf16, 32, NW, SITE>(a, tiles, s);
     if (dt == DT_F32 && hd == 64) return launch_k<float, 64, NW, SITE>(a, tiles, s);
     if (dt == DT_F32 && hd == 32) return launch_k<float, 32, NW, SITE>(a, tiles, s);
-    return hipErrorInvalidValue;
   }
+  return hipErrorInvalidValue;
 }
 
 // Bytes of split partials for `splits` splits of `rows` query rows.
@@ -796,57 +986,83 @@ inline size_t split_bytes(int splits, int rows, int heads, int hd) {
   return (size_t)splits * rows * heads * (hd + 2) * sizeof(float);
 }
 
-// 8 waves (256 queries) per workgroup when that still gives at least 160
-// workgroups; measured on MI355X from 300 to 4096 queries, 256-query
-// workgroups lead from about 2300 queries up (eight waves share each staged
-// K/V tile, which halves the staging work per query). Below that the time is
-// the serial chain of key tiles that one wave walks. Two ways shorten it:
-//  * key groups (bf16, 64-wide heads): the waves of a workgroup split into two
-//    key groups merged through LDS; 64-query workgroups of four waves while
-//    they fit one round on the 256 CUs (128 KiB of LDS: one per CU), else
-//    128-query workgroups of eight waves. Chain: half the key tiles.
-//  * key-range splits over workgroups of four waves, merged by a second
-//    kernel, while all of them fit one round and every split keeps at least
-//    8 key tiles. Chain: 1/splits of the key tiles, plus the merge.
-// Measured on MI355X, 16 heads: both cost about 0.85 us per tile of chain,
-// and splits about 4.5 us more in fixed cost, so key groups are taken unless
-// splits shorten the chain by more than kSplitGainTiles. Examples: self 820
-// queries 10.7 us (key groups) against 13.6 (eight waves, key groups); cross
-// 820 x 1374 keys 14.6 against 19.2 (two splits); 64 x 4096 keys 29.7 against
-// 16.4 (eight splits). Other types and head sizes: four waves, with splits.
+// Launch shapes of the matrix-core path (bf16, 64-wide heads). The time is
+// about the number of key tiles times the rounds of workgroups over 256 CUs
+// times the shape's time per tile, in us, measured on MI355X with 16 heads:
+//   512 queries, 8 waves of 64        1.35   one workgroup per CU
+//   256 queries, 4 waves of 64        1.35   two per CU (0.9 for one alone)
+//   256 queries, 8 waves of 32        0.85   one per CU
+//   128 queries, 8 waves, key groups  0.5    one per CU: half the key tiles per wave
+//    64 queries, 4 waves, key groups  0.35   one per CU
+// The shape with the smallest product is taken. It picks the fastest of the five
+// at 820 (9.4 us; the others 11.6 to 25.2), 1639 (17.5; 23.9 to 41.3), 2000
+// (21.2; 28.1 to 48.2), 6000 (136; 143 to 192), 9831 (361; 379 to 499) and
+// 32768 queries (3388; 3390 to 5636), and ties at 4096 (62.3 and 62.4).
+// Waves of 64 queries take raw passes, whose probabilities are relative to no
+// maximum: with few keys that costs the exactness of the largest one (64 keys:
+// error against float64 2.2e-3 -> 2.4e-3; from 700 keys on no difference), so
+// they are left out below kRawMinTiles.
+//
+// Key-range splits over workgroups of four waves, merged by a second kernel,
+// shorten the chain of key tiles further while all of them fit one round and
+// every split keeps at least 8 key tiles; they cost about 4.5 us more in fixed
+// cost, so they are taken where few queries leave most of the chip idle and
+// splits shorten the chain by more than kSplitGainTiles over key groups (64 x
+// 4096 keys: 29.7 against 16.4 us with eight splits). Other types and head
+// sizes: eight waves of 32 queries from 160 workgroups up (about 2300
+// queries), else four, with splits.
 constexpr long kSplitGainTiles = 5;
+constexpr long kRawMinTiles = 12;
 
 template <int SITE>
 hipError_t launch_site(int dt, int hd, const AttnArgs& a, int heads, float* ws, size_t ws_bytes, hipStream_t s,
                        bool qs) {
-  long t64 = 0, t128 = 0, t256 = 0, kt_min = 1L << 30, kt_max = 0;
+  long t64 = 0, t128 = 0, t256 = 0, t512 = 0, kt_min = 1L << 30, kt_max = 0;
   for (int b = 0; b < a.qs.B; ++b) {
     const int nq = a.qs.off[b + 1] - a.qs.off[b];
     if (nq == 0) continue;
     t64 += (nq + 63) / 64;
     t128 += (nq + 127) / 128;
     t256 += (nq + 255) / 256;
+    t512 += (nq + 511) / 512;
     const long kt = (a.ks.off[b + 1] - a.ks.off[b] + kBKV - 1) / kBKV;
     kt_min = std::min(kt_min, kt);
     kt_max = std::max(kt_max, kt);
   }
+  const bool dma = dt == DT_BF16 && hd == 64;
   // The DMA path addresses a sample's key and value rows with 32-bit offsets
   // from the sample's first row.
-  if (dt == DT_BF16 && hd == 64 && kt_max * kBKV * (int64_t)std::max(a.ldk, a.ldv) * 2 >= (int64_t(1) << 31))
-    return hipErrorInvalidValue;
-  if (t256 * heads >= 160) return launch_a<8, SITE>(dt, hd, a, heads, 1, s, qs);
+  if (dma && kt_max * kBKV * (int64_t)std::max(a.ldk, a.ldv) * 2 >= (int64_t(1) << 31)) return hipErrorInvalidValue;
   int splits = 1;
-  while (splits < 8 && t128 * heads * splits * 2 <= 256 && kt_min >= 16 * splits) splits *= 2;
-  const int rows = a.qs.off[a.qs.B] - a.qs.off[0];
-  while (splits > 1 && (!ws || split_bytes(splits, rows, heads, hd) > ws_bytes)) splits /= 2;
-  if (dt == DT_BF16 && hd == 64 && (kt_max + 1) / 2 - (kt_max + splits - 1) / splits <= kSplitGainTiles) {
-    if (t64 * heads <= 256) return launch_a<4, SITE, 2>(dt, hd, a, heads, 1, s, qs);
-    return launch_a<8, SITE, 2>(dt, hd, a, heads, 1, s, qs);
+  if (t256 * heads < 160) {
+    while (splits < 8 && t128 * heads * splits * 2 <= 256 && kt_min >= 16 * splits) splits *= 2;
+    const int rows = a.qs.off[a.qs.B] - a.qs.off[0];
+    while (splits > 1 && (!ws || split_bytes(splits, rows, heads, hd) > ws_bytes)) splits /= 2;
+    if (dma && (kt_max + 1) / 2 - (kt_max + splits - 1) / splits <= kSplitGainTiles) splits = 1;
   }
+  if (dma && splits == 1) {
+    const auto rounds = [&](long tiles, long wgs) { return (double)((tiles * heads + wgs - 1) / wgs); };
+    enum { Q64K, Q128K, Q256, Q256P, Q512 };
+    const long left = t256 * heads % 512;
+    const double cost[] = {0.35 * rounds(t64, 256), 0.5 * rounds(t128, 256), 0.85 * rounds(t256, 256),
+                           1.35 * (t256 * heads / 512) + (left == 0 ? 0.0 : left <= 256 ? 0.9 : 1.35),
+                           1.35 * rounds(t512, 256)};
+    int pick = Q64K;
+    for (int i = Q128K; i <= (kt_min >= kRawMinTiles ? Q512 : Q256); ++i)
+      if (cost[i] <= cost[pick]) pick = i;
+    switch (pick) {
+      case Q64K: return launch_a<4, SITE, 2>(dt, hd, a, heads, 1, s, qs);
+      case Q128K: return launch_a<8, SITE, 2>(dt, hd, a, heads, 1, s, qs);
+      case Q256: return launch_a<8, SITE>(dt, hd, a, heads, 1, s, qs);
+      case Q256P: return launch_a<4, SITE, 1, 2>(dt, hd, a, heads, 1, s, qs);
+      default: return launch_a<8, SITE, 1, 2>(dt, hd, a, heads, 1, s, qs);
+    }
+  }
+  if (t256 * heads >= 160) return launch_a<8, SITE>(dt, hd, a, heads, 1, s, qs);
   AttnArgs b = a;
   if (splits > 1) {
     b.part_o = ws;
-    b.part_ml = ws + (size_t)splits * rows * heads * hd;
+    b.part_ml = ws + (size_t)splits * (a.qs.off[a.qs.B] - a.qs.off[0]) * heads * hd;
   }
   return launch_a<4, SITE>(dt, hd, b, heads, splits, s, qs);
 }

@@ -381,6 +381,56 @@ def test_attention_bf16_growing_scores(torch, q_lens, k_lens, ramp, ws, prescale
                       workspace=ws, key_ramp=ramp, sample_queries=128, prescaled=prescaled) < 2e-2
 
 
+# Waves of 64 queries (from 12 key tiles up): workgroups of 512 queries (6000 and
+# 6400), of 256 (9000), partial waves and blocks at their end, one more key than
+# 12 and 13 whole tiles; a second sample of one query. With a ramp the sums leave
+# the raw range after some tiles and the workgroup starts over.
+@pytest.mark.parametrize("q_lens,k_lens,ramp", [([6000], [769], 0.0), ([6400], [833], 0.0), ([9000], [705], 0.0),
+                                                ([9011, 1], [1374, 800], 0.0), ([6000], [1374], 1.0),
+                                                ([9000], [1000], 2.0)])
+@pytest.mark.parametrize("prescaled", [False, True])
+def test_attention_bf16_wide_waves(torch, q_lens, k_lens, ramp, prescaled):
+    from paper_2511_22533_amd import f3c
+    assert _attn_case(torch, f3c.F3C_BF16, 16, 64, q_lens, k_lens, seed=sum(q_lens) + sum(k_lens), key_ramp=ramp,
+                      sample_queries=96, prescaled=prescaled) < 2e-2
+
+
+# Scores (base 2) near `level` for every key: above and below what a raw pass
+# takes from its first tile, for a few queries or all of them. And queries that
+# are NaN or infinite, which change no other query of their wave. One launch per
+# shape: 64 and 128 queries with key groups, 256 and 512, key splits.
+@pytest.mark.parametrize("n,nk", [(820, 900), (1639, 900), (3000, 900), (9000, 900), (6000, 900), (200, 4096)])
+@pytest.mark.parametrize("level,bad", [(90.0, False), (-90.0, False), (20.0, True)])
+def test_attention_bf16_score_range(torch, n, nk, level, bad):
+    from paper_2511_22533_amd import f3c
+    rng = np.random.default_rng(n)
+    heads, d = 16, 1024
+    q = rng.standard_normal((n, heads, 64)) * 0.2
+    k = rng.standard_normal((nk, heads, 64))
+    q[:, :, 0] = np.where(rng.random(n) < 0.02, level / 8, 0.5)[:, None] if not bad else level / 8
+    k[:, :, 0] = 8.0
+    q, k = (bf16_round(a.reshape(-1, d).astype(np.float32)) for a in (q, k))
+    v = bf16_round(rng.standard_normal((nk, d)).astype(np.float32))
+    hurt = np.zeros(n, bool)
+    if bad:
+        hurt[[5, 40, n // 2, n - 1]] = True
+        q[[5, n // 2]] = np.nan
+        q[[40, n - 1]] = np.inf
+    o = torch.zeros((n, d), dtype=torch.bfloat16, device="cuda")
+    ws = torch.empty(8 << 20, dtype=torch.float32, device="cuda")
+    say("attention range", n, nk, level, bad)
+    f3c.op_attention(f3c.F3C_BF16, heads, 64, [0, n], [0, nk], to_dev(q, torch.bfloat16), to_dev(k, torch.bfloat16),
+                     to_dev(v, torch.bfloat16), o, workspace=ws, q_prescaled=True)
+    torch.cuda.synchronize()
+    got = o.float().cpu().numpy()
+    assert np.isnan(got[hurt]).all()
+    near = np.unique(np.concatenate([np.flatnonzero(~hurt)[:80], np.flatnonzero(q[:, 0] > 1)[:40],
+                                     rng.choice(n, 60)]))
+    rows = near[~hurt[near]]
+    want = dit.attention(q[rows].astype(np.float64) * 8 * np.log(2.0), k.astype(np.float64), v.astype(np.float64), heads)
+    assert max_rel(got[rows], want) < 2e-2
+
+
 # Two key groups with one or two key tiles: the second group's only tile lies
 # past the end (all keys masked) or is the ragged last one; four-wave
 # workgroups up to 1024 queries, eight-wave ones at 1100.
