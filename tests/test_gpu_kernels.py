@@ -168,8 +168,8 @@ def _gemm_case(torch, dt, epi, M, N, K, seed):
     return got, want
 
 
-# Tile shapes picked: 64 x 64 for the first four, 128 x 128 for 4096 x 1024 x
-# 4096 and 2057 x 4096, 64 x 128 for 1310 x 3072.
+# Tile shapes picked: 64 x 64 for the first three, 64 x 128 for 820 x 3072, 128 x
+# 128 for 4096 x 1024 x 4096, 64 x 128 or 256 x 128 for the last two.
 @pytest.mark.parametrize("M,N,K", [(1, 128, 64), (37, 384, 128), (128, 1024, 1024), (820, 3072, 1024),
                                    (4096, 1024, 4096), (2057, 4096, 1024), (1310, 3072, 1024)])
 @pytest.mark.parametrize("epi", [0, 1, 2])
@@ -179,10 +179,8 @@ def test_gemm_bf16(torch, M, N, K, epi):
     assert max_rel(got, want) < 1e-2
 
 
-# Long K: one round of 64 x 64 workgroups (M up to 1024 at N = 1024) or of
-# 64 x 128 (up to 2048) goes to the kernel whose waves split each K tile in
-# four groups and sum the groups' partial blocks through LDS in a fixed order:
-# ragged M, both tile shapes, every epilogue, and bit-reproducible repeats.
+# Long K: ragged M, the small tile shapes, every epilogue, and bit-reproducible
+# repeats.
 @pytest.mark.parametrize("M,N,K", [(1, 128, 4096), (37, 1024, 4096), (820, 1024, 4096), (1500, 1024, 4096),
                                    (2048, 1024, 4096), (300, 2048, 8192)])
 @pytest.mark.parametrize("epi", [0, 1, 2])
@@ -225,9 +223,8 @@ def _gemm_big_case(torch, epi, M, N, K, seed, rows=None):
     return got, (got[rows], dit.gelu_tanh(ref) if epi == 1 else ref)
 
 
-# Many rows (the 32^3 workload's active sets) go to the 256 x 256 tiles for the
-# QKV projection shape and both MLP projections from 8192 rows: ragged row
-# counts, every epilogue, sampled rows against float64.
+# Many rows (the 32^3 workload's active sets), mostly on 256 x 256 and 256 x 128
+# tiles: ragged row counts, every epilogue, sampled rows against float64.
 @pytest.mark.parametrize("M,N,K", [(8300, 3072, 1024), (9831, 1024, 4096), (16500, 1024, 4096),
                                    (9831, 4096, 1024), (16400, 4096, 1024)])
 @pytest.mark.parametrize("epi", [0, 1, 2])
@@ -236,10 +233,9 @@ def test_gemm_bf16_many_rows(torch, M, N, K, epi):
     assert max_rel(got, want) < 1e-2
 
 
-# The tile choice moves with the row count, not the results: the 256 x 256
-# kernel sums K in the same order with the same instruction as the 128 x 128
-# one, so the rows shared by a run just below the switch and one at it agree
-# bit for bit.
+# The tile choice moves with the row count, not the results: every tile shape
+# sums K in the same order with the same instruction, so the rows shared by two
+# runs agree bit for bit.
 @pytest.mark.parametrize("M,N,K", [(8192, 3072, 1024), (8192, 1024, 4096), (8192, 4096, 1024)])
 @pytest.mark.parametrize("epi", [0, 2])
 def test_gemm_bf16_tile_switch_bit_identical(torch, M, N, K, epi):
@@ -250,7 +246,7 @@ def test_gemm_bf16_tile_switch_bit_identical(torch, M, N, K, epi):
     bias = to_dev(rng.standard_normal(N).astype(np.float32))
     gate = to_dev(rng.standard_normal(N).astype(np.float32))
     outs = []
-    for rows in (M, M - 1):          # at the switch (256 x 256 tiles), just below it
+    for rows in (M, M - 1):
         say("gemm tile switch", epi, rows, N, K)
         if epi == 2:
             r = torch.zeros((rows, N), dtype=torch.float32, device="cuda")
@@ -261,6 +257,58 @@ def test_gemm_bf16_tile_switch_bit_identical(torch, M, N, K, epi):
         torch.cuda.synchronize()
         outs.append(r.float().cpu().numpy())
     assert np.array_equal(outs[0][:M - 1].view(np.uint32), outs[1].view(np.uint32))
+
+
+# The same over all five tile shapes and their edges: a prefix of the rows gives
+# a prefix of the result. (64 x 64 up to 333 rows, 64 x 128 at 1639, 128 x 128 at
+# 2100 and 4097, 256 x 128 at 6000, 256 x 256 for the whole.)
+@pytest.mark.parametrize("N,K", [(1024, 1024), (384, 64), (640, 192)])
+@pytest.mark.parametrize("epi", [0, 1, 2])
+def test_gemm_bf16_row_prefix_bit_identical(torch, N, K, epi):
+    from paper_2511_22533_amd import f3c
+    rng = np.random.default_rng(N + K + epi)
+    M = 9831
+    A = to_dev(rng.standard_normal((M, K)).astype(np.float32), torch.bfloat16)
+    W = to_dev((0.05 * rng.standard_normal((N, K))).astype(np.float32), torch.bfloat16)
+    bias = to_dev(rng.standard_normal(N).astype(np.float32))
+
+    def run(rows):
+        say("gemm rows", epi, rows, N, K)
+        r = torch.zeros((rows, N), dtype=torch.float32 if epi == 2 else torch.bfloat16, device="cuda")
+        f3c.op_gemm(f3c.F3C_BF16, epi, A[:rows], W, bias, **({"resid": r} if epi == 2 else {"out": r}))
+        torch.cuda.synchronize()
+        return r
+
+    whole = run(M)
+    ref = A[::29].double().cpu().numpy() @ W.double().cpu().numpy().T + bias.double().cpu().numpy()
+    assert max_rel(whole[::29].double().cpu().numpy(), dit.gelu_tanh(ref) if epi == 1 else ref) < 1e-2
+    for rows in (1, 63, 64, 65, 333, 1639, 2100, 4097, 6000):
+        assert torch.equal(run(rows), whole[:rows]), rows
+
+
+# Output rows aligned to 8 bytes only, and row strides beyond what 32-bit offsets
+# span within a tile.
+@pytest.mark.parametrize("epi", [0, 1])
+@pytest.mark.parametrize("pad,stride", [(4, 0), (0, (1 << 22) + 8), (12, (1 << 22) + 8)])
+def test_gemm_bf16_strides(torch, epi, pad, stride):
+    from paper_2511_22533_amd import f3c
+    rng = np.random.default_rng(pad + epi)
+    M, N, K = 67, 256, 192
+    a = to_dev(rng.standard_normal((M, K)).astype(np.float32), torch.bfloat16)
+    W = to_dev((0.05 * rng.standard_normal((N, K))).astype(np.float32), torch.bfloat16)
+    bias = to_dev(rng.standard_normal(N).astype(np.float32))
+    want = torch.empty((M, N), dtype=torch.bfloat16, device="cuda")
+    f3c.op_gemm(f3c.F3C_BF16, epi, a, W, bias, out=want)
+    if stride:
+        A = torch.zeros(((M - 1) * stride + K,), dtype=torch.bfloat16, device="cuda").as_strided((M, K), (stride, 1))
+        A.copy_(a)
+    else:
+        A = a
+    out = torch.full((M, N + pad), 7.0, dtype=torch.bfloat16, device="cuda")
+    say("gemm strides", epi, pad, stride)
+    f3c.op_gemm(f3c.F3C_BF16, epi, A, W, bias, out=out[:, :N])
+    torch.cuda.synchronize()
+    assert torch.equal(out[:, :N], want) and bool((out[:, N:] == 7.0).all())
 
 
 @pytest.mark.parametrize("M,N,K", [(1, 128, 32), (300, 384, 128), (513, 512, 128)])
