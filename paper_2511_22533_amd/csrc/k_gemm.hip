@@ -1,4 +1,4 @@
-// Dense projections of the transformer blocks on the 32x32 matrix cores:
+// Dense projections of the transformer blocks on the matrix cores:
 // C = A W^T + bias, A = activations [M][K] (row-major, K contiguous),
 // W = weights [N][K] (torch Linear layout, K contiguous), f32 accumulation.
 // Epilogues fuse the bias with a dtype store (QKV / cross-attention Q / KV),
@@ -8,15 +8,15 @@
 // bf16 (k_gemm_dma): K tiles go HBM -> LDS by DMA into two to four stages, and
 // each MFMA stands in a scheduling group of its own with a fragment read of the
 // next 16-element K-step (and, with more than two stages, its share of the
-// DMA). f32 (k_gemm_f32): 64 x 128 tiles, K staged 128 bytes at a time through
-// registers into padded LDS rows (144-byte stride: the 16-byte fragment reads
-// of 16 consecutive lanes cover all 64 banks once), two tiles ahead.
+// DMA). f32 (k_gemm_f32): K staged 128 bytes at a time through registers into
+// padded LDS rows (144-byte stride: the 16-byte fragment reads of 16
+// consecutive lanes cover all 64 banks once), two tiles ahead.
 //
 // Every output is one workgroup's sum in one K order, the same for every tile
 // shape, so the shape may follow the row count without changing a result.
 //
 // The weight fragment is the MFMA's A operand and the activation fragment its
-// B operand, i.e. each instruction produces a 32 x 32 tile of C^T: a lane then
+// B operand, i.e. each instruction produces a tile of C^T: a lane then
 // holds one activation row and four consecutive output columns per
 // accumulator group, moved as 16-byte vectors. A lane reads 16 contiguous bytes
 // of one row at K-group offset l/32 for both operands; any common assignment
@@ -52,26 +52,25 @@ struct GemmArgs {
   bool out16;                         // stored rows are 16-byte aligned (else 8)
 };
 
-constexpr int kBMF = 64, kBNF = 128;  // workgroup tile of the f32 kernel
-
-template <int EPI, int SITE>
+// f32 projections on the 16x16x4 matrix instruction (the rate of 32x32x2 at a
+// quarter of the tile): four waves in a 2 x 2 arrangement, each with TM x TN
+// tiles. What bounds them at a few hundred rows is the chain of matrix
+// instructions of one wave, so few rows take few tiles per wave: 512 x 128 x 512
+// on 8 workgroups of 64 x 128 (32 instructions of 64 cycles per 32 of K and
+// wave) took 21.6 us and takes 7.3 on 64 of 32 x 32; 1728 x 256 x 1024 39.6 ->
+// 13.6 us (32 x 32), 4096 x 256 x 1024 39.9 -> 22.9 (32 x 64), 4096 x 1024 x 256
+// 25.5 -> 24.0 (64 x 128, two rounds). LDS delivers any of these shapes.
+template <int TM, int TN, int EPI, int SITE>
 __global__ __launch_bounds__(256) void k_gemm_f32(GemmArgs p) {
-  using T = float;
-  constexpr int BM = kBMF, BN = kBNF, WGM = 2, WGN = 2, STAGES = 2, PF = 2;
-  constexpr int NT = 64 * WGM * WGN;                        // threads
-  constexpr int WTM = BM / WGM, WTN = BN / WGN;             // wave tile
-  constexpr int TM = WTM / 32, TN = WTN / 32;               // 32x32 tiles per wave
+  constexpr int WTM = 16 * TM, WTN = 16 * TN, BM = 2 * WTM, BN = 2 * WTN, NT = 256, PF = 2;
   constexpr int CA = BM * 8 / NT, CB = BN * 8 / NT;         // 16-byte chunks per thread
-  constexpr int ES = sizeof(T);
-  constexpr int PER16 = 16 / ES;                            // elements per 16 bytes
-  constexpr int MMA_PER_READ = PER16 / Mfma<T>::E;          // instructions per fragment read
   constexpr int ABUF = BM * kRS, BBUF = BN * kRS;
-  static_assert(CA >= 1 && CB >= 1 && TM >= 1 && TN >= 1, "tile too small for the workgroup");
-  __shared__ __attribute__((aligned(16))) char lds[STAGES * (ABUF + BBUF)];
+  static_assert(CA >= 1 && CB >= 1, "tile too small for the workgroup");
+  __shared__ __attribute__((aligned(16))) char lds[2 * (ABUF + BBUF)];
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = wave / WGN, wn = wave % WGN;
-  const int g = lane >> 5, r32 = lane & 31;
+  const int wm = wave >> 1, wn = wave & 1;
+  const int g = lane >> 4, r16 = lane & 15;
   // Tile of this workgroup. Workgroups go round-robin to the 8 XCDs, each with
   // its own L2; the 1-D grid is remapped so that XCD j gets one contiguous run
   // of a tile order that is column-group major (xq groups of N/BN/xq column
@@ -88,9 +87,9 @@ __global__ __launch_bounds__(256) void k_gemm_f32(GemmArgs p) {
     n0 = (grp * gq + (r - y * gq)) * BN;
     m0 = y * BM;
   }
-  const size_t lda_b = (size_t)p.lda * ES, ldw_b = (size_t)p.ldw * ES;
-  const int KT = (p.K * ES) / kBKB;
-  
+  const size_t lda_b = (size_t)p.lda * 4, ldw_b = (size_t)p.ldw * 4;
+  const int KT = (p.K * 4) / kBKB;
+
   // Rows past M are loaded from row M-1 (always valid) and never stored.
   const char* a_row[CA];
   const char* w_row[CB];
@@ -126,35 +125,33 @@ __global__ __launch_bounds__(256) void k_gemm_f32(GemmArgs p) {
     for (int q = 0; q < CB; ++q) *reinterpret_cast<u32x4*>(Bs + chunk_b[q]) = rb[r][q];
   };
 
-  f32x16 acc[TM][TN];
+  f32x4 acc[TM][TN];
 #pragma unroll
   for (int i = 0; i < TM; ++i)
 #pragma unroll
-    for (int j = 0; j < TN; ++j)
-#pragma unroll
-      for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.0f;
+    for (int j = 0; j < TN; ++j) acc[i][j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
 
+  // A lane reads 16 bytes of row l%16 at K-group l/16 of every 16 floats of K;
+  // element u of both operands meets in instruction u.
   auto compute = [&](int buf) {
     const char* As = lds + buf * (ABUF + BBUF);
     const char* Bs = As + ABUF;
 #pragma unroll
-    for (int ks = 0; ks < kBKB / 32; ++ks) {
-      u32x4 fa[TM], fb[TN];
+    for (int ks = 0; ks < kBKB / 64; ++ks) {
+      f32x4 fa[TM], fb[TN];
 #pragma unroll
       for (int i = 0; i < TM; ++i)
-        fa[i] = *reinterpret_cast<const u32x4*>(As + (wm * WTM + i * 32 + r32) * kRS + ks * 32 + g * 16);
+        fa[i] = *reinterpret_cast<const f32x4*>(As + (wm * WTM + i * 16 + r16) * kRS + ks * 64 + g * 16);
 #pragma unroll
       for (int j = 0; j < TN; ++j)
-        fb[j] = *reinterpret_cast<const u32x4*>(Bs + (wn * WTN + j * 32 + r32) * kRS + ks * 32 + g * 16);
+        fb[j] = *reinterpret_cast<const f32x4*>(Bs + (wn * WTN + j * 16 + r16) * kRS + ks * 64 + g * 16);
 #pragma unroll
-      for (int u = 0; u < MMA_PER_READ; ++u)
+      for (int u = 0; u < 4; ++u)
 #pragma unroll
         for (int i = 0; i < TM; ++i)
 #pragma unroll
-          for (int j = 0; j < TN; ++j) {
-            const float a = __builtin_bit_cast(f32x4, fa[i])[u], w = __builtin_bit_cast(f32x4, fb[j])[u];
-            acc[i][j] = Mfma<T>::mma(w, a, acc[i][j]);   // C^T tile: rows = output columns
-          }
+          for (int j = 0; j < TN; ++j)   // C^T tile: rows = output columns
+            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(fb[j][u], fa[i][u], acc[i][j], 0, 0, 0);
     }
   };
 
@@ -179,43 +176,41 @@ __global__ __launch_bounds__(256) void k_gemm_f32(GemmArgs p) {
   }
   if (kt < KT) step(kt, 0);
 
-  // Epilogue. Tile (i, j), group q: activation row m0 + wm*BM/2 + 32 i + r32,
-  // output columns n0 + wn*BN/2 + 32 j + 8 q + 4 g + (0..3).
+  // Epilogue. Tile (i, j): activation row m0 + wm*WTM + 16 i + r16, output
+  // columns n0 + wn*WTN + 16 j + 4 g + (0..3).
 #pragma unroll
   for (int i = 0; i < TM; ++i) {
-    const int row = m0 + wm * WTM + i * 32 + r32;
+    const int row = m0 + wm * WTM + i * 16 + r16;
     if (row >= p.M) continue;
 #pragma unroll
-    for (int j = 0; j < TN; ++j)
+    for (int j = 0; j < TN; ++j) {
+      const int col = n0 + wn * WTN + j * 16 + 4 * g;
+      const float4 bv = *reinterpret_cast<const float4*>(p.bias + col);
+      const f32x4& c = acc[i][j];
+      float v[4] = {c[0] + bv.x, c[1] + bv.y, c[2] + bv.z, c[3] + bv.w};
+      if constexpr (EPI == EPI_RESID) {
+        float4 gv = make_float4(1.0f, 1.0f, 1.0f, 1.0f);
+        if (p.gate) gv = *reinterpret_cast<const float4*>(p.gate + col);
+        float4* r = reinterpret_cast<float4*>(p.resid + (size_t)row * p.ldr + col);
+        float4 h = *r;
+        h.x += gv.x * v[0];
+        h.y += gv.y * v[1];
+        h.z += gv.z * v[2];
+        h.w += gv.w * v[3];
+        *r = h;
+      } else {
+        if constexpr (EPI == EPI_GELU) {
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int col = n0 + wn * WTN + j * 32 + 8 * q + 4 * g;
-        const float4 bv = *reinterpret_cast<const float4*>(p.bias + col);
-        float v[4] = {acc[i][j][4 * q] + bv.x, acc[i][j][4 * q + 1] + bv.y, acc[i][j][4 * q + 2] + bv.z,
-                      acc[i][j][4 * q + 3] + bv.w};
-        if constexpr (EPI == EPI_RESID) {
-          float4 gv = make_float4(1.0f, 1.0f, 1.0f, 1.0f);
-          if (p.gate) gv = *reinterpret_cast<const float4*>(p.gate + col);
-          float4* r = reinterpret_cast<float4*>(p.resid + (size_t)row * p.ldr + col);
-          float4 h = *r;
-          h.x += gv.x * v[0];
-          h.y += gv.y * v[1];
-          h.z += gv.z * v[2];
-          h.w += gv.w * v[3];
-          *r = h;
-        } else {
-          if constexpr (EPI == EPI_GELU) {
-#pragma unroll
-            for (int e = 0; e < 4; ++e) v[e] = gelu_tanh(v[e]);
-          }
-          if (col < p.oscale_cols) {        // four columns: all in or all out (oscale_cols % 4 == 0)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) v[e] *= p.oscale;
-          }
-          *reinterpret_cast<float4*>(reinterpret_cast<float*>(p.out) + (size_t)row * p.ldo + col) =
-              make_float4(v[0], v[1], v[2], v[3]);
+          for (int e = 0; e < 4; ++e) v[e] = gelu_tanh(v[e]);
         }
+        if (col < p.oscale_cols) {        // four columns: all in or all out (oscale_cols % 4 == 0)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) v[e] *= p.oscale;
+        }
+        *reinterpret_cast<float4*>(reinterpret_cast<float*>(p.out) + (size_t)row * p.ldo + col) =
+            make_float4(v[0], v[1], v[2], v[3]);
       }
+    }
   }
 }
 
@@ -536,6 +531,16 @@ hipError_t launch_dma(const GemmArgs& a0, hipStream_t s) {
   return hipGetLastError();
 }
 
+template <int TM, int TN, int EPI, int SITE>
+hipError_t launch_f32(const GemmArgs& a0, hipStream_t s) {
+  constexpr int BM = 32 * TM, BN = 32 * TN;
+  GemmArgs a = a0;
+  a.xq = choose_xq(a.M, a.N, a.K, 4, BN);
+  if (a.xq < 1 || a.N % BN || (a.N / BN) % a.xq) return hipErrorInvalidValue;
+  launch((k_gemm_f32<TM, TN, EPI, SITE>), dim3((a.N / BN) * ((a.M + BM - 1) / BM)), dim3(256), 0, s, a);
+  return hipGetLastError();
+}
+
 template <typename T, int EPI, int SITE>
 hipError_t launch_t(const GemmArgs& a0, hipStream_t s) {
   GemmArgs a = a0;
@@ -555,10 +560,11 @@ hipError_t launch_t(const GemmArgs& a0, hipStream_t s) {
     }
     return hipErrorInvalidValue;
   } else {
-    a.xq = choose_xq(a.M, a.N, a.K, sizeof(T), kBNF);
-    if (a.xq < 1 || (a.N / kBNF) % a.xq) return hipErrorInvalidValue;
-    launch((k_gemm_f32<EPI, SITE>), dim3((a.N / kBNF) * ((a.M + kBMF - 1) / kBMF)), dim3(256), 0, s, a);
-    return hipGetLastError();
+    // the largest tile that still gives every CU a workgroup (N is a multiple of 128)
+    const auto fills = [&](int bm, int bn) { return (long)((a.M + bm - 1) / bm) * (a.N / bn) >= 256; };
+    if (fills(64, 128)) return launch_f32<2, 4, EPI, SITE>(a, s);
+    if (fills(32, 64)) return launch_f32<1, 2, EPI, SITE>(a, s);
+    return launch_f32<1, 1, EPI, SITE>(a, s);
   }
 }
 

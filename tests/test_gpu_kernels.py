@@ -262,26 +262,30 @@ def test_gemm_bf16_tile_switch_bit_identical(torch, M, N, K, epi):
 # The same over all five tile shapes and their edges: a prefix of the rows gives
 # a prefix of the result. (64 x 64 up to 333 rows, 64 x 128 at 1639, 128 x 128 at
 # 2100 and 4097, 256 x 128 at 6000, 256 x 256 for the whole.)
-@pytest.mark.parametrize("N,K", [(1024, 1024), (384, 64), (640, 192)])
+# f32: 32 x 32 tiles up to 1639 rows (2100 at N = 384), 32 x 64 and 64 x 128 above.
+@pytest.mark.parametrize("dt_name,N,K", [("bf16", 1024, 1024), ("bf16", 384, 64), ("bf16", 640, 192),
+                                         ("f32", 384, 32), ("f32", 640, 96)])
 @pytest.mark.parametrize("epi", [0, 1, 2])
-def test_gemm_bf16_row_prefix_bit_identical(torch, N, K, epi):
+def test_gemm_row_prefix_bit_identical(torch, dt_name, N, K, epi):
     from paper_2511_22533_amd import f3c
     rng = np.random.default_rng(N + K + epi)
     M = 9831
-    A = to_dev(rng.standard_normal((M, K)).astype(np.float32), torch.bfloat16)
-    W = to_dev((0.05 * rng.standard_normal((N, K))).astype(np.float32), torch.bfloat16)
+    dt, tdt = (f3c.F3C_BF16, torch.bfloat16) if dt_name == "bf16" else (f3c.F3C_F32, torch.float32)
+    A = to_dev(rng.standard_normal((M, K)).astype(np.float32), tdt)
+    W = to_dev((0.05 * rng.standard_normal((N, K))).astype(np.float32), tdt)
     bias = to_dev(rng.standard_normal(N).astype(np.float32))
 
     def run(rows):
-        say("gemm rows", epi, rows, N, K)
-        r = torch.zeros((rows, N), dtype=torch.float32 if epi == 2 else torch.bfloat16, device="cuda")
-        f3c.op_gemm(f3c.F3C_BF16, epi, A[:rows], W, bias, **({"resid": r} if epi == 2 else {"out": r}))
+        say("gemm rows", dt_name, epi, rows, N, K)
+        r = torch.zeros((rows, N), dtype=torch.float32 if epi == 2 else tdt, device="cuda")
+        f3c.op_gemm(dt, epi, A[:rows], W, bias, **({"resid": r} if epi == 2 else {"out": r}))
         torch.cuda.synchronize()
         return r
 
     whole = run(M)
     ref = A[::29].double().cpu().numpy() @ W.double().cpu().numpy().T + bias.double().cpu().numpy()
-    assert max_rel(whole[::29].double().cpu().numpy(), dit.gelu_tanh(ref) if epi == 1 else ref) < 1e-2
+    tol = 1e-2 if dt_name == "bf16" else 1e-5
+    assert max_rel(whole[::29].double().cpu().numpy(), dit.gelu_tanh(ref) if epi == 1 else ref) < tol
     for rows in (1, 63, 64, 65, 333, 1639, 2100, 4097, 6000):
         assert torch.equal(run(rows), whole[:rows]), rows
 
