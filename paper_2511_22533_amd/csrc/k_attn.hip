@@ -94,12 +94,18 @@ typedef short i16x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) i16x4 lds_i16x4;
 constexpr float kRescaleLog2 = 8.0f;
 // DMA path: probabilities are taken against a reference max that moves only
-// when a query's row sum passes this. Probabilities (bf16, the exponent range
-// of f32) and sums then stay finite, and their relative rounding does not
-// depend on the reference.
-constexpr float kRowSumLimit = 0x1p80f;
-// Raw passes: the first tile's max (base 2) and the smallest row sum they take.
-constexpr float kRawRange = 40.0f, kRawSumMin = 0x1p-60f;
+// when a query's row sum passes kTileSumLimit times the number of key tiles; it
+// then moves to leave the sum near 2^-kHeadroomLog2, since a move costs all of a
+// wave's queries (1639 x 1639 keys with norms growing 30-fold, us: 25.4; moved to
+// leave a sum near 1 30.2; with a limit of 2^16 31.5). Probabilities (bf16, the
+// exponent range of f32) and sums stay finite, and their relative rounding does
+// not depend on the reference. An unnormalised output is at most the row sum
+// times the largest value: values of 2^100 cannot overflow it in 512 tiles (32768
+// keys), and those of 2^-100 lose nothing that counts.
+constexpr float kTileSumLimit = 0x1p17f, kHeadroomLog2 = 16.0f;
+// Raw passes (see there): the first tile's max (base 2) that they take, and the
+// row sum below which their outputs must be larger than kRawOutMin.
+constexpr float kRawMin = -40.0f, kRawMax = 64.0f, kRawSumMin = 1.0f, kRawOutMin = 0x1p-100f;
 
 struct AttnArgs {
   Segs qs, ks;
@@ -357,12 +363,15 @@ __global__ __launch_bounds__(64 * NW, QB) void k_attn(AttnArgs p) {
     // is one exponential (after a multiply unless the queries were stored
     // scaled), and the reference moves where a sum outgrows it. Raw passes (two
     // blocks, which leave no registers for that): a probability is 2^(s c)
-    // outright. That is the same result up to rounding as long as every sum
-    // stays in a range; a workgroup where one does not takes its queries again
-    // in safe passes, one block after the other. (Known after the first tile as
-    // a rule, by its max: two safe passes take what 32-query waves take. A sum
-    // that leaves the range later costs the raw pass too: 3000 x 1000 keys with
-    // scores up to 1000, 512 queries per workgroup, 65 us.)
+    // outright. That is the same result up to rounding while sums and outputs
+    // neither overflow nor, where the sums are small, come near underflow. A
+    // workgroup where one does takes its queries again in safe passes, one block
+    // after the other. As a rule that is known after the first tile, by its max
+    // (9831 x 9831, 16 heads: 437 us against 359 in raw passes; waves of 32 queries
+    // with four v_dot2 per row sum, in a launch of their own, 417). Scores of about
+    // 110 and more (base 2) after a first tile without are known at the end only
+    // (key norms growing 30-fold: 857 us; 661 in such waves of 32).
+    const float limit = kTileSumLimit * (float)(t_end - t_begin);
     auto prob = [&](float s) { return __builtin_amdgcn_exp2f(QS ? s : s * c); };
     // Steps i = 0, 1, ...: this wave's tile is t_begin + KS*i + kgrp; stage i
     // % NBUF holds the KS tiles of step i. Step i's barrier makes tile i + 1
@@ -427,19 +436,21 @@ __global__ __launch_bounds__(64 * NW, QB) void k_attn(AttnArgs p) {
       };
       // Before the newest probabilities pr (of scores s) enter the PV product.
       // Rare: some query's row sum has outgrown its reference; move the reference
-      // to the largest of these scores or to the sum so far, rescale what was
+      // above the largest of these scores and the sum so far, rescale what was
       // accumulated and the scores taken since (next), and take pr again.
       auto fixup = [&](f32x16 (&s)[PB], f32x16 (&next)[PB], bf16x8 (&pr)[PB][2]) {
         if constexpr (RAW) return;
         // (a NaN sum too: an infinity or NaN among one query's probabilities
         // reaches the row sum of the query 16 lanes away, as 0 * inf)
-        if (__builtin_amdgcn_ballot_w64(!(ls[0][0] <= kRowSumLimit)) != 0) {
+        if (__builtin_amdgcn_ballot_w64(!(ls[0][0] <= limit)) != 0) {
 #pragma unroll
           for (int j = 0; j < PB; ++j) {
             const float mx = max16(s[j]);
-            float tm = l_prev[j] > 1.0f ? __builtin_amdgcn_logf(l_prev[j]) : 0.0f;   // log2
+            float tm = __builtin_amdgcn_logf(l_prev[j]) + kHeadroomLog2;   // log2
+            float tx = fmaxf(mx, __shfl_xor(mx, 32));
             if constexpr (!QS) tm /= c;
-            tm = fmaxf(tm, fmaxf(mx, __shfl_xor(mx, 32)));
+            tx += QS ? kHeadroomLog2 : kHeadroomLog2 / c;
+            tm = fmaxf(0.0f, fmaxf(tm, tx));
             const float alpha = __builtin_amdgcn_exp2f(QS ? -tm : -tm * c);
             m_run[j] += tm;
 #pragma unroll
@@ -587,10 +598,10 @@ __global__ __launch_bounds__(64 * NW, QB) void k_attn(AttnArgs p) {
           l_prev[j] = 0.0f;
         }
         if constexpr (RAW) {
-          float far = 0.0f;
+          bool out = false;                // (a NaN is out)
 #pragma unroll
-          for (int j = 0; j < PB; ++j) far = fmaxf(far, fabsf(m_run[j] * c));
-          if (__builtin_amdgcn_ballot_w64(!(far < kRawRange)) != 0) *flag = 1;
+          for (int j = 0; j < PB; ++j) out = out || !(m_run[j] * c >= kRawMin && m_run[j] * c <= kRawMax);
+          if (__builtin_amdgcn_ballot_w64(out) != 0) *flag = 1;
         }
         if (n_steps > 1) {
           // (0, 0): S(0, 1) is there and no PV is due
@@ -664,13 +675,26 @@ __global__ __launch_bounds__(64 * NW, QB) void k_attn(AttnArgs p) {
         // no DMA may still target this workgroup's LDS when it retires
         wait_vm<0>();
         if constexpr (RAW) {
-          bool in_range = true;            // false for a NaN sum
+          float z = 0.0f;                  // NaN where a sum or output is not finite
+          bool low = false;
 #pragma unroll
-          for (int j = 0; j < PB; ++j) in_range = in_range && l_run[j] > kRawSumMin && l_run[j] < kRowSumLimit;
+          for (int j = 0; j < PB; ++j) {
+            z = __builtin_fmaf(l_run[j], 0.0f, z);
+#pragma unroll
+            for (int h = 0; h < HT; ++h)
+#pragma unroll
+              for (int e = 0; e < 16; ++e) z = __builtin_fmaf(oacc[j][h][e], 0.0f, z);
+            if (__builtin_amdgcn_ballot_w64(l_run[j] < kRawSumMin) != 0) {
+#pragma unroll
+              for (int h = 0; h < HT; ++h)
+#pragma unroll
+                for (int e = 0; e < 16; ++e) low = low || fabsf(oacc[j][h][e]) < kRawOutMin;
+            }
+          }
           __syncthreads();                 // every wave past its last tile read
           if (tid == 0) *flag = 0;
           __syncthreads();
-          if (__builtin_amdgcn_ballot_w64(!in_range) != 0) *flag = 1;
+          if (__builtin_amdgcn_ballot_w64(z != 0.0f || low) != 0) *flag = 1;
           __syncthreads();
           const bool bad = __builtin_amdgcn_readfirstlane(*flag) != 0;
           __syncthreads();                 // read by every wave before a safe pass fetches

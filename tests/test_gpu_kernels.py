@@ -483,6 +483,37 @@ def test_attention_bf16_score_range(torch, n, nk, level, bad):
     assert max_rel(got[rows], want) < 2e-2
 
 
+# Values near both ends of bf16's range, with scores (base 2) near `level` for
+# every key or, late, for all but the first tile's: what the kernels keep
+# unnormalised must neither overflow nor underflow. One launch per shape, as
+# above, and key ranges of one and two tiles; the values are 2^vexp N(0, 1).
+@pytest.mark.parametrize("n,nk", [(820, 900), (1639, 900), (3000, 900), (9000, 900), (6000, 900), (200, 4096),
+                                  (300, 64), (300, 128)])
+@pytest.mark.parametrize("level,late,vexp", [(34.0, False, 100), (60.0, True, 100), (110.0, True, 100),
+                                             (150.0, True, 100), (-34.0, False, -100), (-14.0, False, -100)])
+def test_attention_bf16_value_range(torch, n, nk, level, late, vexp):
+    from paper_2511_22533_amd import f3c
+    rng = np.random.default_rng(n)
+    heads, d = 16, 1024
+    q = rng.standard_normal((n, heads, 64)) * 0.2
+    k = rng.standard_normal((nk, heads, 64))
+    q[:, :, 0] = level / 8
+    k[:, :, 0] = 8.0
+    if late:
+        k[:64, :, 0] = 0.0
+    q, k = (bf16_round(a.reshape(-1, d).astype(np.float32)) for a in (q, k))
+    v = bf16_round(np.ldexp(rng.standard_normal((nk, d)), vexp).astype(np.float32))
+    o = torch.zeros((n, d), dtype=torch.bfloat16, device="cuda")
+    ws = torch.empty(8 << 20, dtype=torch.float32, device="cuda")
+    say("attention values", n, nk, level, late, vexp)
+    f3c.op_attention(f3c.F3C_BF16, heads, 64, [0, n], [0, nk], to_dev(q, torch.bfloat16), to_dev(k, torch.bfloat16),
+                     to_dev(v, torch.bfloat16), o, workspace=ws, q_prescaled=True)
+    torch.cuda.synchronize()
+    rows = np.unique(np.concatenate([np.arange(40), rng.choice(n, 40), [n - 1]]))
+    want = dit.attention(q[rows].astype(np.float64) * 8 * np.log(2.0), k.astype(np.float64), v.astype(np.float64), heads)
+    assert max_rel(o.float().cpu().numpy()[rows], want) < 2e-2
+
+
 # Two key groups with one or two key tiles: the second group's only tile lies
 # past the end (all keys masked) or is the ragged last one; four-wave
 # workgroups up to 1024 queries, eight-wave ones at 1100.
