@@ -16,12 +16,13 @@
 //
 // k_select runs one 1024-thread workgroup per sample with the keys in
 // registers, each wave owning one contiguous run of tokens. The score bin that
-// holds rank c-1 comes from the histogram; the few keys of that bin are ranked
-// against each other (many equal scores: an exact 4 x 8-bit radix select
-// instead), which gives the key of rank c-1. A token is cached if its key is
-// smaller, or equal and among the first r equal keys in token order, which
-// reproduces a stable ascending sort truncated at c.
+// holds rank c-1 comes from the histogram; while a bin holds many keys (crowded
+// or equal scores), its key range is cut into 4096 bins again. The few keys left
+// are ranked against each other, which gives the key of rank c-1. A token is
+// cached if its key is smaller, or equal and among the first r equal keys in token
+// order, which reproduces a stable ascending sort truncated at c.
 #include <mutex>
+#include <type_traits>
 #include <vector>
 
 #include "common.h"
@@ -35,19 +36,23 @@ namespace {
 
 constexpr int kThreads = 1024;       // select: one workgroup per sample
 constexpr int kWaves = kThreads / 64;
+static_assert(kWaves == 16, "the waves' values are reduced in a row of 16 lanes");
 constexpr int kStatThreads = 256;    // score statistics: tokens streamed over the chip
 constexpr int kStatPer = 4;
 constexpr int kChunk = kStatThreads * kStatPer;
 constexpr int kMaxChunks = kMaxTokens / kChunk;
 static_assert(kMaxChunks <= 64, "the partial extremes are reduced in one wave");
 constexpr int kBins = 4096;          // score bins: [0, 1) in steps of 2^-12, NaN and 1 in the last
-constexpr int kCandidates = 512;     // keys of one bin that are ranked against each other
+constexpr int kCandidates = 128;     // keys of one bin that are ranked against each other (a power of two)
 // One workgroup issues an instruction for 32768 tokens in 0.2 us, so for many
 // tokens the keys (two correctly rounded divisions each) and their histogram
 // are worth a grid-wide kernel of their own. Measured on MI355X, batch 1, all
 // kernels, keys in k_select / in k_keys: 8193 tokens 16.2 / 16.1 us, 16384
-// 17.6 / 17.0, 32768 35.0 / 24.8. (Four radix passes over keys in LDS: 4096
-// tokens 17.4 us, now 9.9; 8192 25.3, now 11.9; 32768 70.9, now 24.8.)
+// 17.6 / 17.0, 32768 35.0 / 24.8 (before the scans left the LDS pipe, which takes
+// 0.6 us off either). Against four radix passes over keys in LDS: 512 tokens 9.8
+// -> 6.0 us, 4096 16.4 -> 8.9, 32768 67.2 -> 23.9; scores crowded around one value
+// 9.9 -> 7.7, 17.0 -> 12.5, 68.4 -> 42.2; all equal 9.4 -> 7.6, 16.0 -> 11.0, 64.5
+// -> 35.1.
 constexpr int kFusedTokens = 8192;
 static_assert(kBins <= kFusedTokens, "the histogram lives in the sample's pos rows");
 
@@ -95,6 +100,79 @@ __device__ __forceinline__ float score_of(const float2& va, const float4& ext, f
 // monotonic, so a smaller key never has a larger bin. fminf drops NaN.
 __device__ __forceinline__ int bin_of(uint32_t key) {
   return (int)fminf(__uint_as_float(key & 0x7FFFFFFFu) * (float)kBins, (float)(kBins - 1));
+}
+
+// Smallest key of a bin: its score is exact.
+__device__ __forceinline__ uint32_t bin_start(int bin) {
+  return __float_as_uint((float)bin * (1.0f / (float)kBins)) | 0x80000000u;
+}
+
+// bins[bin] += 1 over the active lanes. Same-address atomics of one instruction
+// serialise, and scores may crowd into one bin (8192 such tokens: 20.4 us, 24.6
+// with an atomic per lane; spread ones 11.8 and 11.6).
+__device__ __forceinline__ void count_one(int* bins, int bin) {
+  const int b0 = __builtin_amdgcn_readfirstlane(bin);
+  const uint64_t m = __ballot(1);
+  if (__ballot(bin != b0) != 0) atomicAdd(&bins[bin], 1);
+  else if ((int)(threadIdx.x & 63) == __ffsll((unsigned long long)m) - 1) atomicAdd(&bins[b0], (int)__popcll(m));
+}
+
+// The same over the lanes with `in`, where a few bins may hold most: the lanes that
+// share the first one's bin add their number at once.
+__device__ __forceinline__ void count_in(int* bins, bool in, int bin) {
+  const uint64_t m = __ballot(in);
+  if (!m) return;
+  const int leader = __ffsll((unsigned long long)m) - 1;
+  const uint64_t same = __ballot(in && bin == __builtin_amdgcn_readlane(bin, leader));
+  const int lane = threadIdx.x & 63;
+  if (in && (lane == leader || !((same >> lane) & 1ull)))
+    atomicAdd(&bins[bin], lane == leader ? (int)__popcll(same) : 1);
+}
+
+// The smallest value in each row of 16 lanes, in all of them.
+__device__ __forceinline__ uint32_t row_min(uint32_t v) {
+  auto with = [&](auto ctrl) {
+    v = min(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, decltype(ctrl)::value, 0xf, 0xf, false));
+  };
+  with(std::integral_constant<int, kDppXor8>{});
+  with(std::integral_constant<int, kDppMirror8>{});
+  with(std::integral_constant<int, kDppXor2>{});
+  with(std::integral_constant<int, kDppXor1>{});
+  return v;
+}
+// Inclusive sums over the lanes of a wave (the LDS pipe's __shfl_up takes six
+// round trips of its latency).
+__device__ __forceinline__ int wave_scan(int x) {
+  auto with = [&](auto ctrl) {
+    x += __builtin_amdgcn_update_dpp(0, x, decltype(ctrl)::value, 0xf, 0xf, false);
+  };
+  with(std::integral_constant<int, 0x111>{});       // row_shr: from 1, 2, 4, 8 lanes before, or 0
+  with(std::integral_constant<int, 0x112>{});
+  with(std::integral_constant<int, 0x114>{});
+  with(std::integral_constant<int, 0x118>{});
+  const int r0 = __builtin_amdgcn_readlane(x, 15), r1 = __builtin_amdgcn_readlane(x, 31);
+  const int r2 = __builtin_amdgcn_readlane(x, 47), row = (threadIdx.x >> 4) & 3;
+  return x + (row == 0 ? 0 : row == 1 ? r0 : row == 2 ? r0 + r1 : r0 + r1 + r2);
+}
+// Sum of cnt over the waves before this one, the same in every lane.
+__device__ __forceinline__ int waves_before(const int* cnt, int wave) {
+  const int w = threadIdx.x & (kWaves - 1);
+  int v = cnt[w];
+  v = w < wave ? v : 0;
+  auto with = [&](auto ctrl) {
+    v += __builtin_amdgcn_update_dpp(0, v, decltype(ctrl)::value, 0xf, 0xf, false);
+  };
+  with(std::integral_constant<int, kDppXor8>{});
+  with(std::integral_constant<int, kDppMirror8>{});
+  with(std::integral_constant<int, kDppXor2>{});
+  with(std::integral_constant<int, kDppXor1>{});
+  return __builtin_amdgcn_readfirstlane(v);
+}
+// Smallest value in the wave.
+__device__ __forceinline__ uint32_t wave_min(uint32_t v) {
+  v = row_min(v);
+  auto row = [&](int l) { return (uint32_t)__builtin_amdgcn_readlane((int)v, l); };
+  return min(min(row(0), row(16)), min(row(32), row(48)));
 }
 
 // The sample's extremes (loV, hiV, loA, hiA) from its partials, by one wave.
@@ -201,13 +279,13 @@ __global__ __launch_bounds__(kStatThreads) void k_keys(float2* __restrict__ va, 
 #pragma unroll
   for (int j = 0; j < kStatPer; ++j) {
     const int l = j * kStatThreads + tid, i = chunk * kChunk + l;
+    const float cs = score_of(p[j], ext, w_a, w_v);
+    const uint32_t k = order_key(cs);
     if (i < N) {
-      const float cs = score_of(p[j], ext, w_a, w_v);
-      const uint32_t k = order_key(cs);
       keys[l] = k;
       if (score) score[base + i] = cs;
-      atomicAdd(&bins[bin_of(k)], 1);
     }
+    if (i < N) count_one(bins, bin_of(k));
   }
   __syncthreads();
   for (int i = tid; i < kBins; i += kStatThreads)
@@ -220,16 +298,18 @@ enum KeySource { KEYS_READY, KEYS_FROM_STATS, KEYS_FROM_SCORES };
 // of 64, at most KR), so ranks in token order need only per-wave counts.
 //   KEYS_READY: k_keys left the keys in the workspace and the histogram in pos.
 //   KEYS_FROM_STATS: keys and histogram are formed here from the pairs.
-//   KEYS_FROM_SCORES: any float32 scores given; always the radix select.
+//   KEYS_FROM_SCORES: any float32 scores given; the first bins cut the range of
+//     all keys.
 template <int SRC, int KR>
 __global__ __launch_bounds__(kThreads) void k_select(const float2* __restrict__ va, const float4* __restrict__ partial,
                                                      int chunks, int N, float w_a, float w_v, Segs n_cache, Segs act,
                                                      int32_t* __restrict__ idx_active, int32_t* __restrict__ pos,
                                                      float* __restrict__ score, const float* __restrict__ given) {
-  __shared__ int bins[SRC == KEYS_FROM_STATS ? kBins : 256];
+  __shared__ int bins[kBins];
   __shared__ uint32_t cand[kCandidates];
   __shared__ int wave_cnt[2][kWaves];
-  __shared__ int sel[2], n_cand;
+  __shared__ uint32_t wave_range[2][kWaves], own_keys[KR][kThreads];
+  __shared__ int sel[3], n_cand;
   __shared__ float4 ext_s;
 
   const int b = blockIdx.x;
@@ -249,7 +329,7 @@ __global__ __launch_bounds__(kThreads) void k_select(const float2* __restrict__ 
 
   const int R = (N + kThreads - 1) / kThreads;
   const int i0 = wave * 64 * R + lane;              // this lane's token of round j: i0 + 64 j
-  uint32_t key[KR];                                 // past the end: 0, never looked at
+  uint32_t key[KR];                                 // past the end the last token's again: see holds
   if (tid == 0) n_cand = 0;
   if constexpr (SRC == KEYS_READY) {
 #pragma unroll
@@ -276,132 +356,123 @@ __global__ __launch_bounds__(kThreads) void k_select(const float2* __restrict__ 
       const int i = i0 + 64 * j;
       const float cs = score_of(p[j], ext, w_a, w_v);
       key[j] = order_key(cs);
-      if (j < R && i < N) {
-        if (score) score[base + i] = cs;
-        atomicAdd(&bins[bin_of(key[j])], 1);
-      }
+      const bool in = j < R && i < N;
+      if (score && in) score[base + i] = cs;
+      if (in) count_one(bins, bin_of(key[j]));
     }
   }
   __syncthreads();
   // whether this lane holds a token in round j
   auto holds = [&](int j) { return j < R && i0 + 64 * j < N; };
 
-  uint32_t kstar = 0;                               // key of rank c-1
-  int r = c;                                        // cached tokens among the keys equal to kstar
-  bool found = false;
-  if constexpr (SRC != KEYS_FROM_SCORES) {
-    // The bin of rank c-1: four consecutive bins per thread, a scan over the
-    // wave, the waves before it added up.
-    int h[4], tot = 0;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      h[e] = SRC == KEYS_READY ? pos[base + 4 * tid + e] : bins[4 * tid + e];
-      tot += h[e];
-    }
-    int x = tot;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-      const int y = __shfl_up(x, o);
-      if (lane >= o) x += y;
-    }
+  // The bin that holds rank r (1-based), given four consecutive bins per thread:
+  // a scan over the wave, the waves before it added up. sel: bin, rank in it, its count.
+  auto locate = [&](const int (&h)[4], int r) {
+    const int tot = h[0] + h[1] + h[2] + h[3];
+    const int x = wave_scan(tot);
     if (lane == 63) wave_cnt[0][wave] = x;
     __syncthreads();
-    int before = x - tot;
-    for (int w = 0; w < wave; ++w) before += wave_cnt[0][w];
-    if (before < c && c <= before + tot) {
+    int before = x - tot + waves_before(wave_cnt[0], wave);
+    if (before < r && r <= before + tot) {
       int d = 0;
 #pragma unroll
       for (int e = 0; e < 3; ++e)
-        if (d == e && before + h[e] < c) {
+        if (d == e && before + h[e] < r) {
           before += h[e];
           d = e + 1;
         }
       sel[0] = 4 * tid + d;
-      sel[1] = c - before;
+      sel[1] = r - before;
+      sel[2] = d == 0 ? h[0] : d == 1 ? h[1] : d == 2 ? h[2] : h[3];
     }
     __syncthreads();
-    const int bin = sel[0], rank = sel[1];          // rank (1-based) inside the bin
+  };
+  // The key of rank c-1 and how many of the keys equal to it are cached: it is the
+  // r-th smallest of the m keys in lo .. hi.
+  auto first = [](int x) { return __builtin_amdgcn_readfirstlane(x); };   // the same in every lane
+  uint32_t lo = 0, hi = 0xFFFFFFFFu;
+  int r = c, m = N;
+  if constexpr (SRC != KEYS_FROM_SCORES) {
+    int h[4];
 #pragma unroll
-    for (int j = 0; j < KR; ++j)
-      if (holds(j) && bin_of(key[j]) == bin) {
-        const int a = atomicAdd(&n_cand, 1);
-        if (a < kCandidates) cand[a] = key[j];
-      }
-    __syncthreads();
-    const int m = n_cand;
-    found = m <= kCandidates;
-    if (found) {
-      if (tid < m) {
-        const uint32_t k = cand[tid];
-        int less = 0, same = 0;
-        for (int i = 0; i < m; ++i) {
-          less += cand[i] < k;
-          same += cand[i] == k;
+    for (int e = 0; e < 4; ++e) h[e] = SRC == KEYS_READY ? pos[base + 4 * tid + e] : bins[4 * tid + e];
+    locate(h, c);
+    const int bin = first(sel[0]);
+    lo = bin_start(bin);
+    if (bin < kBins - 1) hi = bin_start(bin + 1) - 1;
+    r = first(sel[1]);
+    m = first(sel[2]);
+  }
+  if (__builtin_expect(m > kCandidates && lo != hi, 0)) {
+    // Crowded or equal scores. From here on the keys are read from LDS, each thread
+    // its own, in rolled loops: over the registers they cost the ordinary path 1 to
+    // 2 us (masks and spills of KR rounds).
+#pragma unroll
+    for (int j = 0; j < KR; ++j) own_keys[j][tid] = key[j];
+    // A pass leaves 2^20, then 2^8, then one of the 2^32 keys at most.
+    for (int pass = 0; pass < 3 && m > kCandidates && lo != hi; ++pass) {
+      if (pass > 0) {
+        // still many: the range that they span (equal ones are found here)
+        uint32_t least = 0xFFFFFFFFu, most = 0xFFFFFFFFu;   // most: of the complements
+        for (int j = 0; j < R; ++j) {
+          const uint32_t k = own_keys[j][tid];
+          if ((i0 + 64 * j < N) & (k - lo <= hi - lo)) {
+            least = min(least, k);
+            most = min(most, ~k);
+          }
         }
-        if (less < rank && rank <= less + same) {   // equal keys write the same values
-          sel[0] = (int)k;
-          sel[1] = rank - less;
+        least = wave_min(least);
+        most = wave_min(most);
+        if (lane == 0) {
+          wave_range[0][wave] = least;
+          wave_range[1][wave] = most;
         }
       }
       __syncthreads();
-      kstar = (uint32_t)sel[0];
-      r = sel[1];
+      for (int i = tid; i < kBins; i += kThreads) bins[i] = 0;
+      if (pass > 0) {
+        lo = (uint32_t)first((int)row_min(wave_range[0][lane & (kWaves - 1)]));
+        hi = ~(uint32_t)first((int)row_min(wave_range[1][lane & (kWaves - 1)]));
+        if (lo == hi) break;
+      }
+      __syncthreads();
+      const int bits = 32 - __builtin_clz(hi - lo), shift = max(bits - 12, 0);
+      for (int j = 0; j < R; ++j) {
+        const uint32_t k = own_keys[j][tid];
+        count_in(bins, (i0 + 64 * j < N) & (k - lo <= hi - lo), (int)((k - lo) >> shift) & (kBins - 1));
+      }
+      __syncthreads();
+      int h[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) h[e] = bins[4 * tid + e];
+      locate(h, r);
+      lo += (uint32_t)first(sel[0]) << shift;
+      hi = lo + min(hi - lo, (1u << shift) - 1);      // (the bin of the largest key may end past 2^32)
+      r = first(sel[1]);
+      m = first(sel[2]);
     }
   }
-  if (!found) {
-    // Radix select of the key with 0-based rank c-1. The keys may share most
-    // of their bytes, so a wave first merges the lanes that share the bin of
-    // its lowest pending lane, twice, with one LDS atomic per merged bin
-    // (same-address atomics of one instruction would serialise); the lanes
-    // left add their own key.
-    uint32_t prefix = 0, mask = 0;
-    for (int shift = 24; shift >= 0; shift -= 8) {
-      __syncthreads();
-      for (int i = tid; i < 256; i += kThreads) bins[i] = 0;
-      __syncthreads();
+  uint32_t kstar = lo;
+  if (lo != hi) {
 #pragma unroll
-      for (int j = 0; j < KR; ++j) {
-        const bool in = holds(j) && (key[j] & mask) == prefix;
-        const int bin = (int)((key[j] >> shift) & 255u);
-        uint64_t todo = __ballot(in);
-#pragma unroll
-        for (int it = 0; it < 2; ++it) {
-          if (!todo) break;
-          const int leader = __ffsll((unsigned long long)todo) - 1;
-          const int lb = __shfl(bin, leader);
-          const uint64_t same = __ballot(in && bin == lb);
-          if (lane == leader) atomicAdd(&bins[lb], __popcll(same));
-          todo &= ~same;
-        }
-        if ((todo >> lane) & 1ull) atomicAdd(&bins[bin], 1);
+    for (int j = 0; j < KR; ++j)
+      if (holds(j) & (key[j] - lo <= hi - lo)) cand[atomicAdd(&n_cand, 1) & (kCandidates - 1)] = key[j];
+    __syncthreads();
+    if (tid < m) {
+      const uint32_t k = cand[tid];
+      int less = 0, same = 0;
+      for (int i = 0; i < m; ++i) {
+        less += cand[i] < k;
+        same += cand[i] == k;
       }
-      __syncthreads();
-      if (wave == 0) {
-        // lane owns bins 4*lane .. 4*lane+3
-        int h0 = bins[4 * lane], h1 = bins[4 * lane + 1], h2 = bins[4 * lane + 2], h3 = bins[4 * lane + 3];
-        int tot = h0 + h1 + h2 + h3, x = tot;
-#pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-          int y = __shfl_up(x, o);
-          if (lane >= o) x += y;
-        }
-        int before = x - tot;
-        if (before < r && r <= x) {
-          int d = 4 * lane, cum = before;
-          if (cum + h0 >= r) { d += 0; }
-          else if (cum + h0 + h1 >= r) { d += 1; cum += h0; }
-          else if (cum + h0 + h1 + h2 >= r) { d += 2; cum += h0 + h1; }
-          else { d += 3; cum += h0 + h1 + h2; }
-          sel[0] = d;
-          sel[1] = r - cum;
-        }
+      if (less < r && r <= less + same) {             // equal keys write the same values
+        sel[0] = (int)k;
+        sel[1] = r - less;
       }
-      __syncthreads();
-      prefix |= (uint32_t)sel[0] << shift;
-      mask |= 255u << shift;
-      r = sel[1];
     }
-    kstar = prefix;
+    __syncthreads();
+    kstar = (uint32_t)first(sel[0]);
+    r = first(sel[1]);
   }
 
   // Token-order ranks. Per wave the counts of smaller and of equal keys; the
@@ -418,13 +489,8 @@ __global__ __launch_bounds__(kThreads) void k_select(const float2* __restrict__ 
     wave_cnt[1][wave] = n_eq;
   }
   __syncthreads();
-  int less0 = 0, eq0 = 0;
-  for (int w = 0; w < wave; ++w) {
-    less0 += wave_cnt[0][w];
-    eq0 += wave_cnt[1][w];
-  }
-  less0 = __builtin_amdgcn_readfirstlane(less0);
-  eq0 = __builtin_amdgcn_readfirstlane(eq0);
+  const int less0 = waves_before(wave_cnt[0], wave);
+  int eq0 = waves_before(wave_cnt[1], wave);
   int next = row0 + min(wave * 64 * R, N) - less0 - min(eq0, r);   // row of this wave's first active token
   const uint64_t below = (1ull << lane) - 1ull;
 #pragma unroll
@@ -524,7 +590,8 @@ hipError_t launch_select(const float* v_cache, const float* v_prev, int B, int N
     launch(kernel, dim3(B), dim3(kThreads), 0, s, (const float2*)va, (const float4*)partial, chunks, N, w_a, w_v,
            n_cache, act, idx_active, pos, score, (const float*)nullptr);
   };
-  if (N <= 4 * kThreads) select(k_select<KEYS_FROM_STATS, 4>);
+  if (N <= kThreads) select(k_select<KEYS_FROM_STATS, 1>);
+  else if (N <= 4 * kThreads) select(k_select<KEYS_FROM_STATS, 4>);
   else if (fused) select(k_select<KEYS_FROM_STATS, 8>);
   else if (N <= 16 * kThreads) select(k_select<KEYS_READY, 16>);
   else select(k_select<KEYS_READY, 32>);
@@ -537,7 +604,10 @@ hipError_t launch_select_scores(const float* scores, int B, int N, const Segs& n
     launch(kernel, dim3(B), dim3(kThreads), 0, s, (const float2*)nullptr, (const float4*)nullptr, 0, N, 0.0f, 0.0f,
            n_cache, act, idx_active, pos, (float*)nullptr, scores);
   };
-  if (N <= 8 * kThreads) select(k_select<KEYS_FROM_SCORES, 8>);
+  if (N <= kThreads) select(k_select<KEYS_FROM_SCORES, 1>);
+  else if (N <= 4 * kThreads) select(k_select<KEYS_FROM_SCORES, 4>);
+  else if (N <= 8 * kThreads) select(k_select<KEYS_FROM_SCORES, 8>);
+  else if (N <= 16 * kThreads) select(k_select<KEYS_FROM_SCORES, 16>);
   else select(k_select<KEYS_FROM_SCORES, 32>);
   return hipGetLastError();
 }
