@@ -179,7 +179,7 @@ __global__ __launch_bounds__(64 * NW, QB) void k_attn(AttnArgs p) {
   const int head = logical / (ntq * nsp);
   const int rem = logical - head * ntq * nsp;
   const int tq = rem / nsp, sp = rem - tq * nsp;
-  const int b = find_segment(p.tile_off, p.qs.B, tq);
+  const int b = find_segment_wave(p.tile_off, p.qs.B, tq);
   const int qt = tq - p.tile_off[b];
   const int q_begin = p.qs.off[b], nq = p.qs.off[b + 1] - q_begin;
   const int k_begin = p.ks.off[b], nk = p.ks.off[b + 1] - k_begin;
@@ -1025,7 +1025,11 @@ inline size_t split_bytes(int splits, int rows, int heads, int hd) {
 // Waves of 64 queries take raw passes, whose probabilities are relative to no
 // maximum: with few keys that costs the exactness of the largest one (64 keys:
 // error against float64 2.2e-3 -> 2.4e-3; from 700 keys on no difference), so
-// they are left out below kRawMinTiles.
+// they are left out below kRawMinTiles. There the rounds' own cost counts too
+// (launch, queries, first tile, output): the other three take 3.9 + 0.27 t, 5.25 +
+// 0.43 t and 4.4 + 0.92 t us per round at t key tiles, a fit that picks the fastest
+// at every measured shape of 200 to 32768 queries (9831 x 64 keys: 256 queries
+// 17.6 us, 128 with key groups 30.8; x 257 27.3 and 37.3; x 600 41 and 47).
 //
 // Key-range splits over workgroups of four waves, merged by a second kernel,
 // shorten the chain of key tiles further while all of them fit one round and
@@ -1071,9 +1075,14 @@ hipError_t launch_site(int dt, int hd, const AttnArgs& a, int heads, float* ws, 
     const double cost[] = {0.35 * rounds(t64, 256), 0.5 * rounds(t128, 256), 0.85 * rounds(t256, 256),
                            1.35 * (t256 * heads / 512) + (left == 0 ? 0.0 : left <= 256 ? 0.9 : 1.35),
                            1.35 * rounds(t512, 256)};
+    const double t = (double)kt_max;        // (the fit holds for few tiles in every sample)
+    const double few[] = {(3.9 + 0.27 * t) * rounds(t64, 256), (5.25 + 0.43 * t) * rounds(t128, 256),
+                          (4.4 + 0.92 * t) * rounds(t256, 256)};
     int pick = Q64K;
-    for (int i = Q128K; i <= (kt_min >= kRawMinTiles ? Q512 : Q256); ++i)
-      if (cost[i] <= cost[pick]) pick = i;
+    for (int i = Q128K; i <= (kt_min >= kRawMinTiles ? Q512 : Q256); ++i) {
+      const double* c = kt_max >= kRawMinTiles ? cost : few;
+      if (c[i] <= c[pick]) pick = i;
+    }
     switch (pick) {
       case Q64K: return launch_a<4, SITE, 2>(dt, hd, a, heads, 1, s, qs);
       case Q128K: return launch_a<8, SITE, 2>(dt, hd, a, heads, 1, s, qs);

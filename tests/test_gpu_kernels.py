@@ -882,6 +882,23 @@ def _kernel_us(torch, fn, calls=20, repeats=7):
     return best
 
 
+# Few keys and many queries: the launch shape follows what a round of workgroups
+# costs besides its key tiles, so one key tile is not slower than three. (9831
+# queries: 18 and 22 us; with the shape of longer key ranges 31 and 33.)
+@pytest.mark.parametrize("n", [6000, 9831])
+def test_attention_few_keys_cost(torch, n):
+    from paper_2511_22533_amd import f3c
+    g = torch.Generator(device="cuda").manual_seed(n)
+    q, k, v = (torch.randn(rows, 1024, generator=g, device="cuda").bfloat16() for rows in (n, 192, 192))
+    o = torch.empty_like(q)
+    us = {}
+    for nk in (64, 192):
+        say("attention few keys cost", n, nk)
+        us[nk] = _kernel_us(torch, lambda: f3c.op_attention(f3c.F3C_BF16, 16, 64, [0, n], [0, nk], q, k[:nk], v[:nk], o,
+                                                            q_prescaled=True))
+    assert us[64] < 0.9 * us[192], us
+
+
 # Scores crowded into one bin, or all equal, take a few more passes over the keys
 # than spread ones (512 tokens: 7.7 and 7.6 us against 6.0); a radix select behind
 # the histogram took 2.2 times the spread ones' time.
