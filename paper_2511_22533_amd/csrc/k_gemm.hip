@@ -492,16 +492,21 @@ inline int choose_xq(int M, int N, int K, int es, int BN) {
 // Tile shapes of the bf16 kernel, by a cost model in us: a fixed cost, per 1024
 // of K a fixed cost, a cost per round of 256 workgroups (a partial round costs a
 // whole one) and one per 256 workgroups' load, and per round and load the
-// epilogue; a least-squares fit to 225 measured shapes on MI355X (width 512 to
-// 2048, its four projections, 200 to 32768 rows; rms 5 to 8%). Over those shapes
-// it picks a tile 0.6% slower than the best in the mean, 10% at worst.
-struct TileCost { int bm, bn; double fixed, k, k_round, k_load, round, load_resid, load_gelu; };
+// epilogue; a least-squares fit to 663 measured calls on MI355X (widths 128 to 8192
+// and 24576 columns, K = 64 to 8192, 64 to 65536 rows, every epilogue). Over those
+// it picks a tile 0.3% slower than the best in the mean (the four projections of
+// widths 512 to 2048: 0.1%), 11% at worst up to 8192 columns and K >= 128; the
+// residual epilogue into 24576 columns is the worst, 32% at 1374 rows (its writes,
+// which the model takes for a load, take longer in narrow row pieces). A fit
+// without the store's load, to widths 512 to 2048 alone, was up to 46% off: 32768
+// x 4096 x 64 113 us (77 now), 5496 x 24576 x 1024 residual 589 us (443).
+struct TileCost { int bm, bn; double fixed, k, k_round, k_load, round, load_store, load_resid, load_gelu; };
 constexpr TileCost kTileCost[] = {
-    {256, 256, 1.91, 0.00, 15.02, 8.19, 6.26, 16.38, 6.27},
-    {256, 128, 2.02, 0.00, 7.72, 4.86, 3.46, 7.60, 3.17},
-    {128, 128, 2.08, 0.00, 5.04, 2.40, 1.88, 3.02, 1.43},
-    {64, 128, 2.64, 0.73, 3.14, 1.41, 0.47, 1.00, 0.48},
-    {64, 64, 2.31, 0.91, 1.89, 0.76, 0.40, 0.56, 0.23},
+    {256, 256, 1.31, 0.00, 13.73, 10.63, 8.11, 0.00, 14.74, 5.98},
+    {256, 128, 0.88, 0.00, 6.98, 6.45, 4.49, 1.30, 8.56, 4.15},
+    {128, 128, 0.88, 0.00, 4.59, 3.61, 2.95, 0.00, 3.91, 1.54},
+    {64, 128, 1.89, 0.43, 3.61, 1.08, 0.96, 0.11, 1.15, 0.56},
+    {64, 64, 1.76, 0.58, 2.48, 0.20, 0.86, 0.00, 0.64, 0.20},
 };
 
 inline int choose_tiles(int M, int N, int K, int epi) {
@@ -512,7 +517,7 @@ inline int choose_tiles(int M, int N, int K, int epi) {
     if (N % m.bn) continue;
     const double load = (double)((M + m.bm - 1) / m.bm) * (N / m.bn) / 256.0, rounds = std::ceil(load), k = K / 1024.0;
     const double t = m.fixed + k * (m.k + m.k_round * rounds + m.k_load * load) + m.round * rounds +
-                     (epi == EPI_RESID ? m.load_resid : epi == EPI_GELU ? m.load_gelu : 0.0) * load;
+                     (epi == EPI_RESID ? m.load_resid : epi == EPI_GELU ? m.load_gelu : m.load_store) * load;
     if (best < 0 || t < best_t) {
       best = c;
       best_t = t;

@@ -93,3 +93,31 @@ def oracle_selection(v_cache: np.ndarray, v_prev: np.ndarray, n_cache, omega=0.7
             s = ssc.cache_score(v_cache[b], v_prev[b], omega)
             out.append((s, ssc.select(s, int(n_cache[b]))[1]))
     return out
+
+
+GEMM_TILES = [(256, 256), (256, 128), (128, 128), (64, 128), (64, 64)]
+
+
+def gemm_tile(M: int, N: int, K: int, epi: int) -> int:
+    """Index into GEMM_TILES of the tile that the library's bf16 projections take (choose_tiles in k_gemm.hip, with
+    the table as it stands there)."""
+    import math
+    import os
+    import re
+    from paper_2511_22533_amd import build
+    with open(os.path.join(build.CSRC, "k_gemm.hip")) as f:
+        text = f.read()
+    body = text[text.index("kTileCost[] = {"):]
+    rows = re.findall(r"\{([-\d., ]+)\}", body[:body.index("};")])
+    best = None
+    for i, row in enumerate(rows):
+        bm, bn, fixed, k, k_round, k_load, rnd, store, resid, gelu = (float(x) for x in row.split(","))
+        assert (bm, bn) == GEMM_TILES[i]
+        if N % int(bn):
+            continue
+        load = math.ceil(M / bm) * (N // int(bn)) / 256.0
+        t = fixed + K / 1024.0 * (k + k_round * math.ceil(load) + k_load * load) + rnd * math.ceil(load) + (
+            resid if epi == 2 else gelu if epi == 1 else store) * load
+        if best is None or t < best[0]:
+            best = (t, i)
+    return best[1]
