@@ -882,6 +882,39 @@ def _kernel_us(torch, fn, calls=20, repeats=7):
     return best
 
 
+# Row strides beyond 32-bit offsets, of either operand, with both tiles such calls
+# take: bit for bit the contiguous call's result. The large one is not held to the
+# smallest tile (1000 x 4096 x 1024: 14 us, 21 with 64 x 64, contiguous 13).
+@pytest.mark.parametrize("which,M,N,K,epi", [("A", 1000, 4096, 1024, 0), ("A", 130, 256, 64, 2), ("W", 300, 256, 192, 1)])
+def test_gemm_bf16_wide_rows(torch, which, M, N, K, epi):
+    from paper_2511_22533_amd import f3c
+    g = torch.Generator(device="cuda").manual_seed(M)
+    a = torch.randn(M, K, generator=g, device="cuda").bfloat16()
+    w = (0.05 * torch.randn(N, K, generator=g, device="cuda")).bfloat16()
+    bias = torch.randn(N, generator=g, device="cuda")
+
+    def wide(x):
+        stride = (1 << 22) + 8
+        y = torch.empty((x.shape[0] - 1) * stride + K, dtype=x.dtype, device="cuda").as_strided(x.shape, (stride, 1))
+        y.copy_(x)
+        return y
+
+    def call(A, W):
+        r = torch.zeros(M, N, dtype=torch.float32 if epi == 2 else torch.bfloat16, device="cuda")
+        run = lambda: f3c.op_gemm(f3c.F3C_BF16, epi, A, W, bias, **({"resid": r} if epi == 2 else {"out": r}))
+        say("gemm wide rows", which, M, N, K, epi)
+        run()
+        torch.cuda.synchronize()
+        return run, r
+
+    _, want = call(a, w)
+    A, W = (wide(a), w) if which == "A" else (a, wide(w))
+    run, got = call(A, W)
+    assert torch.equal(got, want)
+    if M == 1000:
+        assert _kernel_us(torch, run) < 1.45 * _kernel_us(torch, call(a, w)[0])
+
+
 # Few keys and many queries: the launch shape follows what a round of workgroups
 # costs besides its key tiles, so one key tile is not slower than three. (9831
 # queries: 18 and 22 us; with the shape of longer key ranges 31 and 33.)
