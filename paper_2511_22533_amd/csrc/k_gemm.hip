@@ -56,11 +56,12 @@ struct GemmArgs {
 // f32 projections on the 16x16x4 matrix instruction (the rate of 32x32x2 at a
 // quarter of the tile): four waves in a 2 x 2 arrangement, each with TM x TN
 // tiles. What bounds them at a few hundred rows is the chain of matrix
-// instructions of one wave, so few rows take few tiles per wave: 512 x 128 x 512
-// on 8 workgroups of 64 x 128 (32 instructions of 64 cycles per 32 of K and
-// wave) took 21.6 us and takes 7.3 on 64 of 32 x 32; 1728 x 256 x 1024 39.6 ->
-// 13.6 us (32 x 32), 4096 x 256 x 1024 39.9 -> 22.9 (32 x 64), 4096 x 1024 x 256
-// 25.5 -> 24.0 (64 x 128, two rounds). LDS delivers any of these shapes.
+// instructions of one wave, so few rows take few tiles per wave; at many rows
+// the matrix rate, which more waves per SIMD keep up. Measured, us, with one
+// 64 x 128 workgroup of 32x32x2 / the workgroup tile taken: 512 x 128 x 512 21.6 /
+// 5.9 (32 x 32), 1728 x 256 x 1024 39.6 / 13.5 (32 x 32), 4096 x 256 x 1024 39.9 /
+// 22.8 (32 x 64), 9831 x 1024 x 1024 171 / 170 (64 x 64; 176 with 64 x 128), 9831 x
+// 4096 x 1024 664 / 645, 32768 x 1024 x 1024 538 / 532 (64 x 64).
 template <int TM, int TN, int EPI, int SITE>
 __global__ __launch_bounds__(256) void k_gemm_f32(GemmArgs p) {
   constexpr int WTM = 16 * TM, WTN = 16 * TN, BM = 2 * WTM, BN = 2 * WTN, NT = 256, PF = 2;
@@ -527,6 +528,33 @@ inline int choose_tiles(int M, int N, int K, int epi, std::initializer_list<int>
   return best;
 }
 
+// Tile shapes of the f32 kernel (N is a multiple of 128), by the same model without
+// the epilogue: a fit to 52 measured calls (128 to 24576 columns, K = 32 to 4096,
+// 257 to 32768 rows) that picks a tile 0.4% slower than the best of six in the
+// mean, 3% at worst (128 x 128 leads from 9831 x 4096 columns on, by up to 3%; 64 x
+// 128 and 128 x 64 nowhere).
+struct F32TileCost { int bm, bn; double fixed, k, k_round, k_load, load; };
+constexpr F32TileCost kF32TileCost[] = {
+    {64, 64, 2.65, 4.97, 15.26, 0.28, 1.01},
+    {32, 64, 2.45, 3.40, 8.41, 0.14, 0.55},
+    {32, 32, 2.35, 1.56, 4.81, 0.00, 0.27},
+};
+
+inline int choose_f32_tiles(int M, int N, int K) {
+  int best = 0;
+  double best_t = 0.0;
+  for (int c = 0; c < 3; ++c) {
+    const F32TileCost& m = kF32TileCost[c];
+    const double load = (double)((M + m.bm - 1) / m.bm) * (N / m.bn) / 256.0;
+    const double t = m.fixed + K / 1024.0 * (m.k + m.k_round * std::ceil(load) + m.k_load * load) + m.load * load;
+    if (c == 0 || t < best_t) {
+      best = c;
+      best_t = t;
+    }
+  }
+  return best;
+}
+
 template <int BM, int BN, int WGM, int WGN, int STAGES, int OCC, int EPI, int SITE, bool WIDE = false>
 hipError_t launch_dma(const GemmArgs& a0, hipStream_t s) {
   GemmArgs a = a0;
@@ -571,10 +599,10 @@ hipError_t launch_t(const GemmArgs& a0, hipStream_t s) {
     }
     return hipErrorInvalidValue;
   } else {
-    // the largest tile that still gives every CU a workgroup (N is a multiple of 128)
-    const auto fills = [&](int bm, int bn) { return (long)((a.M + bm - 1) / bm) * (a.N / bn) >= 256; };
-    if (fills(64, 128)) return launch_f32<2, 4, EPI, SITE>(a, s);
-    if (fills(32, 64)) return launch_f32<1, 2, EPI, SITE>(a, s);
+    switch (choose_f32_tiles(a.M, a.N, a.K)) {
+      case 0: return launch_f32<2, 2, EPI, SITE>(a, s);
+      case 1: return launch_f32<1, 2, EPI, SITE>(a, s);
+    }
     return launch_f32<1, 1, EPI, SITE>(a, s);
   }
 }

@@ -121,3 +121,24 @@ def gemm_tile(M: int, N: int, K: int, epi: int) -> int:
         if best is None or t < best[0]:
             best = (t, i)
     return best[1]
+
+
+F32_GEMM_TILES = [(64, 64), (32, 64), (32, 32)]
+
+
+def gemm_f32_tile(M: int, N: int, K: int) -> int:
+    """The same for the f32 projections (choose_f32_tiles), an index into F32_GEMM_TILES."""
+    import math
+    import os
+    import re
+    from paper_2511_22533_amd import build
+    with open(os.path.join(build.CSRC, "k_gemm.hip")) as f:
+        text = f.read()
+    body = text[text.index("kF32TileCost[] = {"):]
+    rows = [[float(x) for x in r.split(",")] for r in re.findall(r"\{([-\d., ]+)\}", body[:body.index("};")])]
+    assert [(r[0], r[1]) for r in rows] == F32_GEMM_TILES
+    t = []
+    for bm, bn, fixed, k, k_round, k_load, ld in rows:
+        load = math.ceil(M / bm) * (N // int(bn)) / 256.0
+        t.append(fixed + K / 1024.0 * (k + k_round * math.ceil(load) + k_load * load) + ld * load)
+    return t.index(min(t))
