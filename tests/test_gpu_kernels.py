@@ -13,7 +13,8 @@
 import numpy as np
 import pytest
 
-from helpers import bf16_round, max_rel, oracle_selection, say, to_dev
+from helpers import (F32_GEMM_TILES, GEMM_TILES, bf16_round, gemm_f32_tile, gemm_tile, max_rel, oracle_selection, say,
+                     to_dev)
 from oracle import dit, ssc
 from paper_2511_22533_amd import synth
 
@@ -168,8 +169,8 @@ def _gemm_case(torch, dt, epi, M, N, K, seed):
     return got, want
 
 
-# Tile shapes picked: 64 x 64 for the first three, 64 x 128 for 820 x 3072, 128 x
-# 128 for 4096 x 1024 x 4096, 64 x 128 or 256 x 128 for the last two.
+# Few and ragged rows, one and several column tiles, one K tile and many (the tile
+# shapes follow the size: see gemm_tile; the tests below cross all of them).
 @pytest.mark.parametrize("M,N,K", [(1, 128, 64), (37, 384, 128), (128, 1024, 1024), (820, 3072, 1024),
                                    (4096, 1024, 4096), (2057, 4096, 1024), (1310, 3072, 1024)])
 @pytest.mark.parametrize("epi", [0, 1, 2])
@@ -179,7 +180,7 @@ def test_gemm_bf16(torch, M, N, K, epi):
     assert max_rel(got, want) < 1e-2
 
 
-# Long K: ragged M, the small tile shapes, every epilogue, and bit-reproducible
+# Long K: ragged M, few rows, every epilogue, and bit-reproducible
 # repeats.
 @pytest.mark.parametrize("M,N,K", [(1, 128, 4096), (37, 1024, 4096), (820, 1024, 4096), (1500, 1024, 4096),
                                    (2048, 1024, 4096), (300, 2048, 8192)])
@@ -223,8 +224,8 @@ def _gemm_big_case(torch, epi, M, N, K, seed, rows=None):
     return got, (got[rows], dit.gelu_tanh(ref) if epi == 1 else ref)
 
 
-# Many rows (the 32^3 workload's active sets), mostly on 256 x 256 and 256 x 128
-# tiles: ragged row counts, every epilogue, sampled rows against float64.
+# Many rows (the 32^3 workload's active sets), on 256 x 256 and 256 x 128 tiles:
+# ragged row counts, every epilogue, sampled rows against float64.
 @pytest.mark.parametrize("M,N,K", [(8300, 3072, 1024), (9831, 1024, 4096), (16500, 1024, 4096),
                                    (9831, 4096, 1024), (16400, 4096, 1024)])
 @pytest.mark.parametrize("epi", [0, 1, 2])
@@ -234,35 +235,41 @@ def test_gemm_bf16_many_rows(torch, M, N, K, epi):
 
 
 # The tile choice moves with the row count, not the results: every tile shape
-# sums K in the same order with the same instruction, so the rows shared by two
-# runs agree bit for bit.
-@pytest.mark.parametrize("M,N,K", [(8192, 3072, 1024), (8192, 1024, 4096), (8192, 4096, 1024)])
-@pytest.mark.parametrize("epi", [0, 2])
-def test_gemm_bf16_tile_switch_bit_identical(torch, M, N, K, epi):
+# sums K in the same order with the same instruction, so runs on different tiles
+# agree bit for bit in the rows they share. The row counts take all five tiles, for
+# every epilogue and over 32 and 64 K tiles.
+@pytest.mark.parametrize("N,K,rows", [(1024, 4096, (9831, 8191, 4096, 2047, 820)),
+                                      (512, 2048, (16400, 9831, 8191, 4095, 2048))])
+@pytest.mark.parametrize("epi", [0, 1, 2])
+def test_gemm_bf16_tile_switch_bit_identical(torch, N, K, rows, epi):
     from paper_2511_22533_amd import f3c
+    assert {gemm_tile(m, N, K, epi) for m in rows} == set(range(len(GEMM_TILES)))
+    M = rows[0]
     rng = np.random.default_rng(M + N + epi)
     A = to_dev(rng.standard_normal((M, K)).astype(np.float32), torch.bfloat16)
     W = to_dev((0.05 * rng.standard_normal((N, K))).astype(np.float32), torch.bfloat16)
     bias = to_dev(rng.standard_normal(N).astype(np.float32))
     gate = to_dev(rng.standard_normal(N).astype(np.float32))
-    outs = []
-    for rows in (M, M - 1):
-        say("gemm tile switch", epi, rows, N, K)
+    whole = None
+    for m in rows:
+        say("gemm tile switch", epi, m, N, K, GEMM_TILES[gemm_tile(m, N, K, epi)])
         if epi == 2:
-            r = torch.zeros((rows, N), dtype=torch.float32, device="cuda")
-            f3c.op_gemm(f3c.F3C_BF16, 2, A[:rows], W, bias, resid=r, gate=gate)
+            r = torch.zeros((m, N), dtype=torch.float32, device="cuda")
+            f3c.op_gemm(f3c.F3C_BF16, 2, A[:m], W, bias, resid=r, gate=gate)
         else:
-            r = torch.empty((rows, N), dtype=torch.bfloat16, device="cuda")
-            f3c.op_gemm(f3c.F3C_BF16, epi, A[:rows], W, bias, out=r)
+            r = torch.empty((m, N), dtype=torch.bfloat16, device="cuda")
+            f3c.op_gemm(f3c.F3C_BF16, epi, A[:m], W, bias, out=r)
         torch.cuda.synchronize()
-        outs.append(r.float().cpu().numpy())
-    assert np.array_equal(outs[0][:M - 1].view(np.uint32), outs[1].view(np.uint32))
+        if whole is None:
+            whole = r
+        assert torch.equal(r.view(torch.int32 if epi == 2 else torch.int16),
+                           whole[:m].view(torch.int32 if epi == 2 else torch.int16)), m
 
 
-# The same over all five tile shapes and their edges: a prefix of the rows gives
-# a prefix of the result. (64 x 64 up to 333 rows, 64 x 128 at 1639, 128 x 128 at
-# 2100 and 4097, 256 x 128 at 6000, 256 x 256 for the whole.)
-# f32: 32 x 32 tiles up to 1639 rows (2100 at N = 384), 32 x 64 and 64 x 128 above.
+# The same at the edges of tiles, with short K and column counts that the wider
+# tiles do not divide, and in f32: a prefix of the rows gives a prefix of the
+# result. (Plain stores of 1024 columns take all five tiles, f32 calls of 640 columns
+# all three.)
 @pytest.mark.parametrize("dt_name,N,K", [("bf16", 1024, 1024), ("bf16", 384, 64), ("bf16", 640, 192),
                                          ("f32", 384, 32), ("f32", 640, 96)])
 @pytest.mark.parametrize("epi", [0, 1, 2])
@@ -282,6 +289,10 @@ def test_gemm_row_prefix_bit_identical(torch, dt_name, N, K, epi):
         torch.cuda.synchronize()
         return r
 
+    shapes = {gemm_tile(m, N, K, epi) if dt_name == "bf16" else gemm_f32_tile(m, N, K)
+              for m in (M, 1, 63, 64, 65, 333, 1639, 2100, 4097, 6000)}
+    assert (dt_name, N, epi) != ("bf16", 1024, 0) or shapes == set(range(len(GEMM_TILES)))
+    assert (dt_name, N) != ("f32", 640) or shapes == set(range(len(F32_GEMM_TILES)))
     whole = run(M)
     ref = A[::29].double().cpu().numpy() @ W.double().cpu().numpy().T + bias.double().cpu().numpy()
     tol = 1e-2 if dt_name == "bf16" else 1e-5
@@ -435,8 +446,8 @@ def test_attention_bf16_growing_scores(torch, q_lens, k_lens, ramp, ws, prescale
 
 # Waves of 64 queries (from 12 key tiles up): workgroups of 512 queries (6000 and
 # 6400), of 256 (9000), partial waves and blocks at their end, one more key than
-# 12 and 13 whole tiles; a second sample of one query. With a ramp the sums leave
-# the raw range after some tiles and the workgroup starts over.
+# 12 and 13 whole tiles; a second sample of one query. With a ramp the sums
+# overflow after some tiles and the workgroup starts over.
 @pytest.mark.parametrize("q_lens,k_lens,ramp", [([6000], [769], 0.0), ([6400], [833], 0.0), ([9000], [705], 0.0),
                                                 ([9011, 1], [1374, 800], 0.0), ([6000], [1374], 1.0),
                                                 ([9000], [1000], 2.0)])
@@ -913,6 +924,21 @@ def test_gemm_bf16_wide_rows(torch, which, M, N, K, epi):
     assert torch.equal(got, want)
     if M == 1000:
         assert _kernel_us(torch, run) < 1.45 * _kernel_us(torch, call(a, w)[0])
+
+
+# More samples than the lookup of a workgroup's sample walks one by one, with empty
+# ones at both ends and in between; bf16 on each path, and f32.
+@pytest.mark.parametrize("dt_name,hd", [("bf16", 64), ("bf16", 32), ("f32", 64)])
+@pytest.mark.parametrize("B", [5, 64])
+def test_attention_many_samples(torch, dt_name, hd, B):
+    from paper_2511_22533_amd import f3c
+    rng = np.random.default_rng(B + hd)
+    q_lens = [int(x) for x in rng.integers(0, 150, B)]
+    q_lens[0] = q_lens[1] = q_lens[-1] = 0
+    q_lens[B // 2] = 129
+    k_lens = [int(x) for x in rng.integers(1, 200, B)]
+    dt = f3c.F3C_BF16 if dt_name == "bf16" else f3c.F3C_F32
+    assert _attn_case(torch, dt, 4, hd, q_lens, k_lens, seed=B) < (2e-2 if dt_name == "bf16" else 1e-4)
 
 
 # Few keys and many queries: the launch shape follows what a round of workgroups
