@@ -416,12 +416,15 @@ __global__ __launch_bounds__(64 * WGM * WGN, OCC) void k_gemm_dma(GemmArgs p) {
   }
 #pragma unroll
   for (int i = 0; i < TM; ++i) {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
 #pragma unroll
     for (int j = 0; j < TN; ++j)
 #pragma unroll
       for (int q = 0; q < 4; ++q)
         *(lds_f4*)(uintptr_t)(eb + (uint32_t)(r32 * RS + (j * 32 + 8 * q + 4 * g) * 4)) =
             f32x4{acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]};
+    // (the lanes read what others wrote: the compiler must not reorder, either)
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     const int row0 = m0 + wm * WTM + i * 32 + lane / LPR;
 #pragma unroll
     for (int t = 0; t < 32 / RPI; ++t) {
