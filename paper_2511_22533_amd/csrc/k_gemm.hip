@@ -466,29 +466,27 @@ __global__ __launch_bounds__(64 * WGM * WGN, OCC) void k_gemm_dma(GemmArgs p) {
   }
 }
 
-// Column groups of the XCD tile partition (see k_gemm_f32): over the 8 XCDs, A is
-// read xq times and W 8/xq times in all.
-// Pick the xq (dividing the column-tile count) that minimises that traffic
-// while one XCD's share of W (|W|/xq) stays within half of its 4 MiB L2, so
-// the row panels that follow each other on an XCD find it resident. Where no
-// grouping lets W stay (K >= 4096 and 256 x 256 tiles), each XCD takes whole
-// row panels and the panel's column tiles share its A rows (fc2 at 32768 rows:
-// 270 us against 277 at xq = 4; 9831 rows 97 against 100).
-inline int choose_xq(int M, int N, int K, int es, int BN) {
+// Column groups of the XCD tile partition (see k_gemm_f32): the xq (dividing the
+// column-tile count) with the least traffic beyond the XCDs' L2s. A is read xq
+// times. An XCD's share of W (|W|/xq) is read once where it stays in half of the
+// 4 MiB L2, and otherwise again for each of the XCD's rounds of 32 workgroups.
+// Over 280 measured calls (512 to 24576 columns, K = 512 to 8192, 512 to 32768
+// rows) the pick is 0.2% slower than the best xq in the mean, 4% at worst. A share
+// that stays was preferred whatever A cost before, but for K >= 4096 on 256-wide
+// tiles, where xq was 1; in us: 8192 x 1024 x 8192 157 -> 118, 32768 x 1024 x 2048
+// 169 -> 146, 16384 x 2048 x 2048 149 -> 134, 32768 x 4096 x 4096 1045 -> 997.
+inline int choose_xq(int M, int N, int K, int es, int BM, int BN) {
   const int gx = N / BN;
-  if (es == 2 && K >= 4096 && BN == 256) return 1;
   const double a = (double)M * K * es, w = (double)N * K * es, l2_share = 2.0 * 1024 * 1024;
+  const double rounds = std::max(1.0, (double)((M + BM - 1) / BM) * gx / 256.0);
   int best = 1;
   double best_cost = 0.0;
-  bool best_fits = false;
   for (int q = 1; q <= 8; q *= 2) {
     if (gx % q) continue;
-    const bool fits = w / q <= l2_share;
-    const double cost = a * q + w * (8.0 / q);
-    if (q == 1 || (fits && !best_fits) || (fits == best_fits && cost <= best_cost)) {
+    const double cost = a * q + (w / q <= l2_share ? w * (8.0 / q) : 8.0 * rounds * (w / q));
+    if (q == 1 || cost < best_cost) {
       best = q;
       best_cost = cost;
-      best_fits = fits;
     }
   }
   return best;
@@ -561,7 +559,7 @@ inline int choose_f32_tiles(int M, int N, int K) {
 template <int BM, int BN, int WGM, int WGN, int STAGES, int OCC, int EPI, int SITE, bool WIDE = false>
 hipError_t launch_dma(const GemmArgs& a0, hipStream_t s) {
   GemmArgs a = a0;
-  a.xq = choose_xq(a.M, a.N, a.K, 2, BN);
+  a.xq = choose_xq(a.M, a.N, a.K, 2, BM, BN);
   if (a.xq < 1 || a.N % BN || (a.N / BN) % a.xq || a.K % 64) return hipErrorInvalidValue;
   launch((k_gemm_dma<BM, BN, WGM, WGN, STAGES, OCC, EPI, SITE, WIDE>), dim3((a.N / BN) * ((a.M + BM - 1) / BM)),
          dim3(64 * WGM * WGN), 0, s, a);
@@ -572,7 +570,7 @@ template <int TM, int TN, int EPI, int SITE>
 hipError_t launch_f32(const GemmArgs& a0, hipStream_t s) {
   constexpr int BM = 32 * TM, BN = 32 * TN;
   GemmArgs a = a0;
-  a.xq = choose_xq(a.M, a.N, a.K, 4, BN);
+  a.xq = choose_xq(a.M, a.N, a.K, 4, BM, BN);
   if (a.xq < 1 || a.N % BN || (a.N / BN) % a.xq) return hipErrorInvalidValue;
   launch((k_gemm_f32<TM, TN, EPI, SITE>), dim3((a.N / BN) * ((a.M + BM - 1) / BM)), dim3(256), 0, s, a);
   return hipGetLastError();
