@@ -158,10 +158,11 @@ def hbm_sweep():
       pack_occ      B*V*(4 + 1/8)             (f32 logit per voxel in, one bit out)
       dyn_voxels    B*V/4                     (two packed grids in, Eq. 1)
     Times are per launch with no host gaps (the launches of each size are
-    captured in one graph). A selection call is two kernels: the scoring pass
-    streams the caches over the whole chip (its share: B*N*64 bytes), then one
-    workgroup per sample selects from its keys held in LDS, so below about
-    256 samples that second kernel's time is latency."""
+    captured in one graph). A selection call is two kernels, three above 8192
+    tokens: the scoring pass streams the caches over the whole chip (its share:
+    B*N*64 bytes), above 8192 tokens a second pass forms the keys, then one
+    workgroup per sample selects from its keys held in registers, so below about
+    256 samples that last kernel's time is latency."""
     import torch
     from paper_2511_22533_amd import f3c, synth
     torch.cuda.set_device(0)

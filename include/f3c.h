@@ -308,9 +308,10 @@ int f3c_profile_reset(f3c_state* s);
  * idx_active (int32, sum(N - c_b) rows, ascending per sample), pos int32 [B][N]
  * and, if score != NULL, score float32 [B][N] (for samples with c_b > 0).
  * workspace: device scratch, 256-byte aligned, at least
- * f3c_op_select_workspace_bytes(B, N) bytes (the per-token magnitudes and the
- * partial extremes passed from the streaming scoring pass to the per-sample
- * selection); caller-owned, contents undefined after the call. Errors:
+ * f3c_op_select_workspace_bytes(B, N) bytes (the per-token magnitudes or keys
+ * and the partial extremes passed from the streaming passes to the per-sample
+ * selection); caller-owned, contents undefined after the call. Above 8192
+ * tokens pos serves as scratch before its values are written. Errors:
  * F3C_EINVAL (shapes, NULL or misaligned buffers, omega outside [0, 1]),
  * F3C_ENOMEM (workspace too small). */
 int f3c_op_select_workspace_bytes(int32_t batch, int32_t n_tokens, size_t* bytes);
@@ -363,7 +364,8 @@ int f3c_op_gemm(int32_t dtype, int32_t epilogue, int32_t M, int32_t N, int32_t K
  * log2(e) / sqrt(head_dim), the softmax scale in base-2 units (as the step's
  * projections store them, rounded once); 0 for plain queries. The result is
  * softmax(Q K^T / sqrt(head_dim)) V either way (Sec. 4.2: attention over the
- * active tokens).
+ * active tokens). Any finite scores; bf16 values between 2^-100 and 2^100 in
+ * magnitude neither overflow nor lose precision before the normalisation.
  * workspace (device, 16-byte aligned, may be NULL) lets launches with few
  * query tiles and long key ranges split the key range over workgroups (when
  * that shortens each wave's chain of key tiles by enough to repay the merge):

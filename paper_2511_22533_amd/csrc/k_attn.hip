@@ -3,13 +3,14 @@
 // attention runs on the active subset only) and for cross-attention from the
 // active tokens to the image-condition tokens.
 //
-// Online softmax over key/value tiles of 64 staged in LDS (V stored
-// transposed). Each wavefront owns 32 queries and computes S^T = K Q^T, so a
-// lane holds one query's scores for 16 of every 32 keys: the running max and
-// sum are per-lane values combined with a single cross-half exchange
-// (lane l with l ^ 32). The same accumulator layout feeds O^T = V^T P^T as the
-// B operand without any data movement; the K-slot order of P (keys
-// 8*(e/4) + 4*(l/32) + e%4) is matched when the V^T fragment is read.
+// Online softmax over key/value tiles of 64 staged in LDS. Each wavefront owns 32
+// queries, or two blocks of 32, and computes S^T = K Q^T, so a lane holds one
+// query's scores for 16 of every 32 keys of a block: the running max and sum are
+// per-lane values combined with a single cross-half exchange (lane l with l ^ 32).
+// The same accumulator layout feeds O^T = V^T P^T as the B operand without any
+// data movement; the K-slot order of P (keys 8*(e/4) + 4*(l/32) + e%4) is matched
+// when the V^T fragment is read: from row-major tiles by the LDS transpose read
+// (bf16 with 64-wide heads), else from tiles stored transposed.
 //
 // Pipelining, bf16 with 64-wide heads (the transformer's case): K and V tiles
 // go from global memory straight into five LDS buffers (four with key groups)
@@ -63,8 +64,9 @@ __device__ __forceinline__ void static_for(F f) {
 
 // max(a, b, c) as one v_max3_f32. fmaxf on MFMA results costs three
 // instructions each (both inputs are first quieted with v_max x, x, since the
-// compiler cannot prove they are not signalling NaNs); the scores here are
-// finite or -inf, never NaN.
+// compiler cannot prove they are not signalling NaNs). A NaN score is passed over
+// unless all three are; its query's probabilities and sum are NaN all the same,
+// and a pass tests for sums that are not below its limit.
 __device__ __forceinline__ float max3(float a, float b, float c) {
   float r;
   asm("v_max3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));

@@ -222,7 +222,9 @@ __global__ __launch_bounds__(256) void k_gemm_f32(GemmArgs p) {
 // write and each round's fill and drain beside it; at a few hundred rows it is
 // the chain of K tiles of one workgroup. Against the kernels these replaced
 // (register-staged 128 x 128, 64 x 128 and 64 x 64 tiles, a 256 x 256 kernel
-// with hand-written K-steps, four K-groups per tile for K = 4096), in us:
+// with hand-written K-steps, four K-groups per tile for K = 4096), each call
+// repeated by itself on the same operands (in a step, behind other
+// kernels, the large ones gain less: fc1 and fc2 at 32768 rows 15 us together), us:
 //   QKV   32768 x 3072 x 1024  235 -> 192   9831 rows  78 -> 63   1639 rows 21.7 -> 16.0
 //   fc1   32768 x 4096 x 1024  317 -> 295   9831 rows 115 -> 103  820 rows  14.6 -> 12.0
 //   fc2   32768 x 1024 x 4096  288 -> 270   9831 rows 114 -> 97   4096 rows 46 -> 38

@@ -9,7 +9,7 @@
 namespace f3c {
 
 constexpr int kMaxBatch = 64;          // samples per step (segment tables travel by value)
-constexpr int kMaxTokens = 32768;      // tokens per sample (the selector keeps one sample's keys in LDS)
+constexpr int kMaxTokens = 32768;      // tokens per sample (one workgroup holds a sample's keys, 32 per thread)
 
 // Segment table passed by value: sample b owns rows [off[b], off[b+1]).
 struct Segs {
@@ -25,19 +25,21 @@ enum Epilogue { EPI_STORE = 0, EPI_GELU = 1, EPI_RESID = 2 };
 enum Site { SITE_OP = 0, SITE_QKV, SITE_O, SITE_Q, SITE_CO, SITE_FC1, SITE_FC2, SITE_COND, SITE_SELF, SITE_CROSS };
 
 // Stability score + lowest-score selection: a streaming statistics pass over
-// all tokens, then one workgroup per sample. v_cache, v_prev: f32 [B][N][8].
+// all tokens, above 8192 tokens a second one that forms the keys and a score
+// histogram, then one workgroup per sample. v_cache, v_prev: f32 [B][N][8].
 // n_cache: per-sample cached counts (by value). act: active-row offsets (by
 // value). Writes idx_active[act.off[b] + r] (ascending token index of the r-th
 // active token), pos[b*N + i] (packed row or -1) and, when score != nullptr,
 // the float32 score of every token (only for c_b > 0). workspace (256-byte
 // aligned, select_workspace_bytes(B, N) bytes) holds the per-token magnitude
-// pairs and the per-workgroup extremes between the two kernels.
+// pairs or keys and the per-workgroup extremes between the kernels; pos holds
+// the histograms before its own values.
 size_t select_workspace_bytes(int B, int N);
 hipError_t launch_select(const float* v_cache, const float* v_prev, int B, int N, float w_a, float w_v,
                          const Segs& n_cache, const Segs& act, int32_t* idx_active, int32_t* pos,
                          float* score, void* workspace, hipStream_t s);
-// The selection alone from caller-given float32 scores [B][N] (the same keys,
-// radix select and token-order scan; no workspace).
+// The selection alone from caller-given float32 scores [B][N] (the same keys
+// and token-order ranks; no workspace).
 hipError_t launch_select_scores(const float* scores, int B, int N, const Segs& n_cache, const Segs& act,
                                 int32_t* idx_active, int32_t* pos, hipStream_t s);
 // Device address and size of the selection's static scratch on the current

@@ -527,9 +527,10 @@ def test_attention_bf16_value_range(torch, n, nk, level, late, vexp):
 
 # Two key groups with one or two key tiles: the second group's only tile lies
 # past the end (all keys masked) or is the ragged last one; four-wave
-# workgroups up to 1024 queries, eight-wave ones at 1100.
+# workgroups up to 1024 queries, eight-wave ones in the last two cases (1100
+# queries to one key tile go without key groups).
 @pytest.mark.parametrize("q_lens,k_lens", [([600], [50]), ([600], [64]), ([700], [100]), ([5, 600], [1, 65]),
-                                           ([1100], [50]), ([1100], [100])])
+                                           ([1100], [50]), ([1100], [100]), ([1000, 100], [100, 50])])
 @pytest.mark.parametrize("prescaled", [False, True])
 def test_attention_bf16_key_groups_short_keys(torch, q_lens, k_lens, prescaled):
     from paper_2511_22533_amd import f3c
