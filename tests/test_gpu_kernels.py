@@ -927,22 +927,22 @@ def test_gemm_bf16_wide_rows(torch, which, M, N, K, epi):
         assert _kernel_us(torch, run) < 1.45 * _kernel_us(torch, call(a, w)[0])
 
 
-# Many rows over K = 2048: a weight share that stays in an XCD's L2 is not worth
-# reading the rows twice. (32768 x 1024: 147 us against 271 at K = 4096; 169 with
-# two column groups.)
+# Twice the K takes no more than twice the time: long rows of weights are split over
+# the XCDs in column groups, too. (8192 x 1024: 68 and 121 us; the longer one 161 us
+# when every XCD takes whole row panels.)
 def test_gemm_column_groups_cost(torch):
     from paper_2511_22533_amd import f3c
     g = torch.Generator(device="cuda").manual_seed(0)
-    M, N = 32768, 1024
+    M, N = 8192, 1024
     r = torch.zeros(M, N, device="cuda")
     bias = torch.randn(N, generator=g, device="cuda")
     us = {}
-    for K in (2048, 4096):
+    for K in (4096, 8192):
         A = torch.randn(M, K, generator=g, device="cuda").bfloat16()
         W = (0.05 * torch.randn(N, K, generator=g, device="cuda")).bfloat16()
         say("gemm column groups cost", M, N, K)
         us[K] = _kernel_us(torch, lambda: f3c.op_gemm(f3c.F3C_BF16, 2, A, W, bias, resid=r), calls=5)
-    assert us[2048] < 0.58 * us[4096], us
+    assert us[8192] < 2.04 * us[4096], us
 
 
 # More samples than the lookup of a workgroup's sample walks one by one, with empty
